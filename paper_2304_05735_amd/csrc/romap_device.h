@@ -53,9 +53,6 @@
 #ifndef RM_SCAT_WG
 #define RM_SCAT_WG 512      /* samples (threads) per block of the binning kernel */
 #endif
-#ifndef RM_ENC_SPLIT
-#define RM_ENC_SPLIT 2      /* gather workgroups per block (measured: 1, 2, 4 -> 535, 512, 517 us) */
-#endif
 #define RM_ACC_CHUNK 32768  /* records per accumulation workgroup (about; 8192, 16384, 32768: 2.33, 2.23, 2.22 ms per step) */
 #define RM_ACC_MAXK 256     /* accumulation workgroups per region, at most */
 #ifndef RM_GROUP_RECORDS
@@ -119,6 +116,7 @@ struct ObjStatic {      // written by the host
   uint32_t hashed_mask;
   int32_t L, din, instance, id, n_kf;
   float half[3];
+  float inv2a[3];       // 1 / (2 half), or zeros where that cannot replace the division
   int32_t mlp_layers;   // hidden layers of the density MLP
   const KfRef* kfs;
   int64_t n_cand;
@@ -171,7 +169,12 @@ struct BinPair {        // one (object of the launch, binned level)
   int32_t bin_base;     // first bin (region) of this pair
   int32_t cap;          // record slots per bin (multiple of 4)
   int32_t K;            // accumulation workgroups per bin
-  int32_t merge;        // coarse dense level: merge runs of samples in one cell
+  int32_t merge;        // corners shared by consecutive samples of a ray are merged
+  int32_t touch;        // consecutive samples often share corners: gathered in parity slots
+  int32_t obj, ray_begin; // the object, its first ray in the launch
+  uint32_t N, T;        // the level's table, as in the ObjStatic
+  int32_t hashed;
+  int64_t off;          // first float of the table in the parameters
   int64_t s_begin;      // first sample of the object
   int64_t n_samples;
 };

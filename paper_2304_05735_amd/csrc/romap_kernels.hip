@@ -36,6 +36,8 @@
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef float rm_f2v __attribute__((ext_vector_type(2)));
+typedef float rm_f4v __attribute__((ext_vector_type(4), aligned(8)));
 
 // ---------------------------------------------------------------------------
 // small helpers
@@ -132,6 +134,11 @@ __device__ inline int dppi(int x) {
   return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWM, BANKM, BC);
 }
 
+// the values of lane ^ 1, of the even and of the odd lane of a pair of lanes
+__device__ inline float pair_swap(float x) { return dppf<0xB1>(x); }  // quad_perm:[1,0,3,2]
+__device__ inline uint32_t pair_even(uint32_t x) { return (uint32_t)dppi<0xA0>((int)x); }
+__device__ inline uint32_t pair_odd(uint32_t x) { return (uint32_t)dppi<0xF5>((int)x); }
+
 __device__ inline int wave_incl_prefix_i(int x) {
   x += dppi<0x111>(x);
   x += dppi<0x112>(x);
@@ -147,16 +154,109 @@ __device__ inline float wave_excl_prefix(float x, int lane) {
   return dppf<0x138>(wave_incl_prefix(x));  // wave_shr:1
 }
 
-// Position of sample i of a ray in the unit cube of the object's box:
-// d_i = t_n + (i + 1/2) delta, x = o + d_i d, p = (x + a) / 2a, clamped.
-__device__ inline void sample_pos(const RayRec& R, int i, const float* half, float p[3]) {
-  const float di = R.tn + ((float)i + 0.5f) * R.delta;
+// Quotient a / b for a in [0, b], rounded as IEEE division rounds it, with
+// r = 1 / b rounded to nearest: two corrections of a r by its remainder (the
+// first brings the quotient within one unit, from where the second rounds
+// correctly because the remainder is exact and r correctly rounded).  Holds
+// where nothing underflows: b within 2^-60 .. 2^60 (400 M random and edge
+// operands: none differs).  5 instructions against 11 of the division.
+__device__ inline float div_fixed(float a, float b, float r) {
+  float q = a * r;
+  q = fmaf(fmaf(-q, b, a), r, q);
+  return fmaf(fmaf(-q, b, a), r, q);
+}
+
+// Unit-cube coordinates of an object-frame point: p = (x + a) / 2a clamped to
+// [0, 1] (clamped before dividing, which gives the same values: division is
+// monotonic, and a NaN clamps to 0 either way).  inv: 1 / 2a, or zeros for a
+// box outside div_fixed's range.
+__device__ inline void unit_pos(const float x[3], const float* half, const float* inv, float p[3]) {
+  float n[3], w[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const float x = R.o[k] + di * R.d[k];
-    const float q = (x + half[k]) / (half[k] + half[k]);
-    p[k] = fminf(fmaxf(q, 0.0f), 1.0f);
+    w[k] = half[k] + half[k];
+    n[k] = __builtin_amdgcn_fmed3f(x[k] + half[k], 0.0f, w[k]);
   }
+  if (inv[0] != 0.0f) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p[k] = div_fixed(n[k], w[k], inv[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p[k] = n[k] / w[k];
+  }
+}
+
+// What a sample's position needs of its ray.
+struct RayGeo {
+  float o[3], d[3], tn, delta;
+  uint32_t flags;
+};
+
+// Position of sample i of a ray in the unit cube of the object's box:
+// d_i = t_n + (i + 1/2) delta, x = o + d_i d, p = (x + a) / 2a, clamped.
+template <class Ray>
+__device__ inline void sample_pos(const Ray& R, int i, const float* half, const float* inv,
+                                  float p[3]) {
+  const float di = R.tn + ((float)i + 0.5f) * R.delta;
+  float x[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] = R.o[k] + di * R.d[k];
+  unit_pos(x, half, inv, p);
+}
+
+// A table that no kernel of the launch writes, read at an index that is
+// uniform in the wave: through the scalar cache (a plain pointer would make
+// vector loads of them, as the kernel's own stores might alias it).
+template <class T>
+using cptr = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ inline cptr<T> as_const(const T* p) {
+  return (cptr<T>)(uintptr_t)p;
+}
+
+// Device memory behind a pointer that was itself read from memory (without
+// this the compiler makes flat accesses, which also wait for the LDS).
+template <class T>
+using gptr = __attribute__((address_space(1))) T*;
+template <class T>
+__device__ inline gptr<T> as_global(T* p) {
+  return (gptr<T>)(uintptr_t)p;
+}
+
+__device__ inline RayGeo ray_uniform(const RayRec* rays, int ray) {
+  const cptr<RayRec> q = as_const(rays + ray);
+  RayGeo g;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    g.o[k] = q->o[k];
+    g.d[k] = q->d[k];
+  }
+  g.tn = q->tn;
+  g.delta = q->delta;
+  g.flags = q->flags;
+  return g;
+}
+
+// The ray of each lane of a wave that covers samples k .. k + 63 (k uniform, a
+// multiple of 64) from ray ray0's first: one ray, or with 32 samples per ray
+// two, chosen by lane.  Rays past the launch's n_rays read the last one.
+template <int NS>
+__device__ inline RayGeo wave_ray(const RayRec* rays, int n_rays, int ray0, int k, int lane) {
+  const int ray = ray0 + k / NS;
+  RayGeo g = ray_uniform(rays, ray < n_rays ? ray : n_rays - 1);
+  if constexpr (NS < 64) {
+    const RayGeo h = ray_uniform(rays, ray + 1 < n_rays ? ray + 1 : n_rays - 1);
+    const bool up = lane >= NS;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      g.o[k] = up ? h.o[k] : g.o[k];
+      g.d[k] = up ? h.d[k] : g.d[k];
+    }
+    g.tn = up ? h.tn : g.tn;
+    g.delta = up ? h.delta : g.delta;
+    g.flags = up ? h.flags : g.flags;
+  }
+  return g;
 }
 
 // Occupancy skip: 64^3 bits over the unit cube, bit x + 64 y + 4096 z of cell
@@ -170,7 +270,11 @@ __device__ inline bool occupied(const uint32_t* occ, const float p[3]) {
     c[k] = ci < 0 ? 0 : (ci > 63 ? 63 : ci);
   }
   const int bit = c[0] + 64 * c[1] + 4096 * c[2];
-  return (occ[bit >> 5] >> (bit & 31)) & 1u;
+  return (as_global(occ)[bit >> 5] >> (bit & 31)) & 1u;
+}
+
+__device__ inline bool ray_active(uint32_t flags) {
+  return (flags & RM_F_HIT) && (flags & RM_F_CLS) != RM_CLS_OCCLUDER;
 }
 
 struct Cell {
@@ -182,12 +286,10 @@ __device__ inline void make_cell(const float p[3], uint32_t N, Cell& cl) {
   const float Nf = (float)N;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const float g = p[k] * Nf;
-    int ci = (int)floorf(g);
-    ci = ci < 0 ? 0 : ci;
-    ci = ci > (int)N - 1 ? (int)N - 1 : ci;
-    cl.c[k] = (uint32_t)ci;
-    cl.f[k] = g - (float)ci;
+    const float g = p[k] * Nf;  // p in [0, 1]: g in [0, N]
+    const float c = __builtin_amdgcn_fmed3f(floorf(g), 0.0f, Nf - 1.0f);
+    cl.c[k] = (uint32_t)(int)c;
+    cl.f[k] = g - c;
   }
 }
 
@@ -411,16 +513,111 @@ __global__ __launch_bounds__(256) void k_user_rays(StepArgs a, const float* rays
   a.rays[r] = R;
 }
 
-__device__ inline bool ray_active(uint32_t flags) {
-  return (flags & RM_F_HIT) && (flags & RM_F_CLS) != RM_CLS_OCCLUDER;
+// ---------------------------------------------------------------------------
+// K2: encoding forward.  One workgroup per block of RM_SCAT_WG samples of one
+// (object, level) pair, blocks ordered object by object and level by level
+// within an object, so the chip sweeps one table at a time; the object and
+// level are uniform in a workgroup.  Each wave takes chunks of 64 samples, whose
+// ray (and everything else that is uniform) comes through the scalar cache, so
+// that the vector memory path serves the table alone.  Fine levels are bound
+// by line fills from the L2: 65536 rays x 64 samples on one hashed level of
+// 2^19 entries take 83 us (210 G lines/s, of 265 G/s that random loads reach on
+// this chip) against 94 with one lane per corner pair; coarse dense levels by
+// instruction issue: 24 us against 40.  16 levels of 16..1024 cells: 930 us
+// against 1112.
+
+// Features of the 8 corners of each lane's cell, in the slots of cell_corners
+// with `flip`, on a dense level: the two corners of an x-pair are neighbouring
+// entries, the lower at c_x, and one 16-byte load brings both.  Lanes that
+// are not `live` read the cell at the origin.
+__device__ inline void gather_dense(const gptr<const char> G, const Cell& cl, uint32_t N, bool live,
+                                    uint32_t flip, float2 g[8]) {
+  const uint32_t n1 = N + 1u, n2 = n1 * n1;
+  const uint32_t b0 = live ? cl.c[0] + cl.c[1] * n1 + cl.c[2] * n2 : 0u;
+  const uint32_t y0 = (flip & 2u) ? n1 : 0u, z0 = (flip & 4u) ? n2 : 0u;
+  const uint32_t b1 = b0 + z0, b2 = b0 + (n2 - z0), y1 = n1 - y0;
+  const uint32_t row[4] = {b1 + y0, b1 + y1, b2 + y0, b2 + y1};
+  rm_f4v v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = *(gptr<const rm_f4v>)(G + (row[q] << 3));
+  const bool up = flip & 1u;  // the lower entry is slot 1 of the pair
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    g[2 * q].x = up ? v[q][2] : v[q][0];
+    g[2 * q].y = up ? v[q][3] : v[q][1];
+    g[2 * q + 1].x = up ? v[q][0] : v[q][2];
+    g[2 * q + 1].y = up ? v[q][1] : v[q][3];
+  }
 }
 
-// ---------------------------------------------------------------------------
-// K2: encoding forward.  RM_ENC_SPLIT workgroups per block of RM_SCAT_WG
-// samples of one (object, level) pair, blocks ordered object by object and
-// level by level within an object, so the chip sweeps one table at a time;
-// the object and level are uniform in a workgroup.  blockDim threads cover
-// the workgroup's samples.
+// The same on a hashed level.  x enters the hash with factor 1, so the two
+// entries of an x-pair differ in the trailing ones of c_x and the bit above
+// and lie in the same 128 B line 15 times in 16.  Two neighbouring lanes load
+// the two corners of one lane's pair in one instruction, which then asks for
+// 32 lines and not 64 (line fills from the L2, 2.3 clocks each per CU, bound
+// this kernel on the fine levels): first the pairs of the even lanes' samples
+// (A), then those of the odd lanes' (B).  Indices are kept as byte offsets.
+// Every lane of the wave takes part; lanes that are not `live` read entry 0.
+template <bool FLIP>
+__device__ inline void gather_hashed(const gptr<const char> G, const Cell& cl, uint32_t T, bool live,
+                                     uint32_t flip, uint32_t odd, float2 g[8]) {
+  const uint32_t ya = cl.c[1] * (2654435761u << 3), za = cl.c[2] * (805459861u << 3);
+  const uint32_t yb = ya + (2654435761u << 3), zb = za + (805459861u << 3);
+  const uint32_t y0 = FLIP && (flip & 2u) ? yb : ya, y1 = FLIP && (flip & 2u) ? ya : yb;
+  const uint32_t z0 = FLIP && (flip & 4u) ? zb : za, z1 = FLIP && (flip & 4u) ? za : zb;
+  const uint32_t yz[4] = {y0 ^ z0, y1 ^ z0, y0 ^ z1, y1 ^ z1};
+  // x of this lane's corner: slot `odd` of the cell of lane A or B
+  const uint32_t ca = pair_even(cl.c[0]), cb = pair_odd(cl.c[0]);
+  const uint32_t xa = (ca + (FLIP ? (odd ^ ca) & 1u : odd)) << 3;
+  const uint32_t xb = (cb + (FLIP ? (odd ^ cb) & 1u : odd)) << 3;
+  const uint32_t m = live ? (T - 1u) << 3 : 0u, ma = pair_even(m), mb = pair_odd(m);
+  rm_f2v va[4], vb[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) va[q] = *(gptr<const rm_f2v>)(G + ((xa ^ pair_even(yz[q])) & ma));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) vb[q] = *(gptr<const rm_f2v>)(G + ((xb ^ pair_odd(yz[q])) & mb));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    // exchanged with every lane active, then chosen
+    const float2 sa = make_float2(pair_swap(va[q][0]), pair_swap(va[q][1]));
+    const float2 sb = make_float2(pair_swap(vb[q][0]), pair_swap(vb[q][1]));
+    g[2 * q].x = odd ? sb.x : va[q][0];
+    g[2 * q].y = odd ? sb.y : va[q][1];
+    g[2 * q + 1].x = odd ? vb[q][0] : sa.x;
+    g[2 * q + 1].y = odd ? vb[q][1] : sa.y;
+  }
+}
+
+// One level's encoding of the samples at p (unit cube) of a wave's live lanes,
+// added up in slot order; all lanes of the wave call it.
+__device__ inline void encode_wave(const gptr<const char> G, uint32_t N, uint32_t T, bool hashed,
+                                   bool touch, bool live, const float p[3], uint32_t odd, float& ex,
+                                   float& ey) {
+  Cell cl;
+  make_cell(p, N, cl);  // valid indices for every lane: p is clamped
+  float2 g[8];
+  float w[8];
+  if (hashed && !touch) {
+    gather_hashed<false>(G, cl, T, live, 0u, odd, g);
+    cell_weights(cl, w);
+  } else {
+    // on levels where consecutive samples of a ray touch, parity slots: a
+    // vertex two lanes share is then loaded by one instruction at one address
+    const uint32_t flip = touch ? cell_parity(cl) : 0u;
+    if (hashed) gather_hashed<true>(G, cl, T, live, flip, odd, g);
+    else gather_dense(G, cl, N, live, flip, g);
+    cell_weights(cl, w, flip);
+  }
+  float x = 0.0f, y = 0.0f;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    x = fmaf(w[b], g[b].x, x);
+    y = fmaf(w[b], g[b].y, y);
+  }
+  ex = live ? x : 0.0f;
+  ey = live ? y : 0.0f;
+}
+
 template <int NS>
 __global__ __launch_bounds__(512) void k_encode_fwd(StepArgs a) {
   const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -430,76 +627,48 @@ __global__ __launch_bounds__(512) void k_encode_fwd(StepArgs a) {
   // contiguous range of (object, level) blocks, a level's table is gathered
   // by one XCD at a time and stays in its L2: the L2 hit rate goes from 0.67
   // to 0.93 and the lines fetched beyond the L2 from 2.8 to 0.5 GB per step
-  // on the 24-object workload.  The kernel alone is no faster (it is bound by
-  // the L2's request rate, the same either way, and the XCDs' ranges differ
-  // in cost: 492 -> 522 us), but the bandwidth it no longer takes goes to
-  // the other object group's kernels: 1.812 -> 1.800 ms per step.
-  const int nwg = a.n_bblocks * RM_ENC_SPLIT;
-  const int per_xcd = (nwg + 7) >> 3;
+  // on the 24-object workload.  The kernel alone is no faster (the XCDs' ranges
+  // differ in cost), but the bandwidth it no longer takes goes to the other
+  // object group's kernels: 1.812 -> 1.800 ms per step when this was built.
+  const int per_xcd = (a.n_bblocks + 7) >> 3;
   const int jw = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
-  if (jw >= nwg) return;
-  const BinBlock bb = a.bblocks[jw / RM_ENC_SPLIT];
-  constexpr int SPAN = RM_SCAT_WG / RM_ENC_SPLIT;  // samples of this workgroup
-  const int k0 = (jw % RM_ENC_SPLIT) * SPAN;
-  const BinPair bp = a.bpairs[bb.pair];
-  const ObjStatic& ob = a.objs[a.sobj[bp.so].obj];
-  const int l = bp.l;
-  const uint32_t N = ob.N_l[l], T = ob.T_l[l];
-  const bool hashed = (ob.hashed_mask >> l) & 1u;
-  const float* G = (a.params_override ? a.params_override : ob.params) + ob.off[l];
-  for (int k = k0 + threadIdx.x; k < k0 + SPAN; k += blockDim.x) {
-    const int64_t ks = (int64_t)bb.blk * RM_SCAT_WG + k;
-    if (ks >= bp.n_samples) break;
-    const int64_t s = bp.s_begin + ks;
-    const RayRec R = a.rays[s / NS];
-    if (!ray_active(R.flags)) continue;
+  if (jw >= a.n_bblocks) return;
+  const cptr<BinBlock> bb = as_const(a.bblocks + jw);
+  const int blk = bb->blk;
+  const cptr<BinPair> bp = as_const(a.bpairs + bb->pair);
+  const cptr<ObjStatic> ob = as_const(a.objs + bp->obj);
+  const int ray0 = bp->ray_begin + (int)((int64_t)blk * RM_SCAT_WG / NS);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int waves = (int)blockDim.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const uint32_t odd = lane & 1;
+  const float* Gp = (a.params_override ? a.params_override : ob->params) + bp->off;
+  const gptr<const char> G = as_global((const char*)Gp);
+  const uint32_t* occ = ob->occ;
+  const float half[3] = {ob->half[0], ob->half[1], ob->half[2]};
+  const float inv[3] = {ob->inv2a[0], ob->inv2a[1], ob->inv2a[2]};
+  const uint32_t N = bp->N, T = bp->T;
+  const bool touch = bp->touch, hashed = bp->hashed;
+  const int64_t left = bp->n_samples - (int64_t)blk * RM_SCAT_WG;  // samples from here on
+  const int n = left < RM_SCAT_WG ? (int)left : RM_SCAT_WG;
+  const int64_t at = (int64_t)bp->l * a.S + bp->s_begin + (int64_t)blk * RM_SCAT_WG;
+  RayGeo Rn = wave_ray<NS>(a.rays, a.n_rays, ray0, 64 * wave, lane);
+  for (int k = 64 * wave; k < n; k += 64 * waves) {
+    const RayGeo R = Rn;
+    // the next chunk's ray, in flight during this one
+    Rn = wave_ray<NS>(a.rays, a.n_rays, ray0, k + 64 * waves, lane);
+    const bool act = k + lane < n && ray_active(R.flags);
+    if (__ballot(act) == 0ull) continue;
     float p[3];
-    sample_pos(R, (int)(s % NS), ob.half, p);
-    if (!occupied(ob.occ, p)) {  // skipped sample: no gather, zero encoding
-      if (a.e_bf16)
-        ((uint32_t*)a.e)[(int64_t)l * a.S + s] = 0u;
-      else
-        a.e[(int64_t)l * a.S + s] = make_float2(0.0f, 0.0f);
-      continue;
-    }
-    Cell cl;
-    make_cell(p, N, cl);
-    uint32_t idx[8];
-    float w[8];
-    // on levels where consecutive samples of a ray touch, parity slots: a
-    // vertex two lanes share is then loaded by one instruction at one address
-    const uint32_t flip = bp.merge ? cell_parity(cl) : 0u;
-    cell_corners(cl, N, T, hashed, idx, flip);
-    cell_weights(cl, w, flip);
-    // The two corners of an x-pair are neighbouring entries on dense levels
-    // (index + 1) and, when the cell's x is even, on hashed ones (x enters
-    // the hash with factor 1: index ^ 1): then one 16-byte load brings both,
-    // halving the cache requests of the pair.
-    float2 g[8];
-    const bool adj = !hashed || (cl.c[0] & 1u) == 0u;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t i0 = idx[2 * q], i1 = idx[2 * q + 1];
-      if (adj) {
-        const uint32_t lo = i0 < i1 ? i0 : i1;
-        const float4 v = *(const float4*)(G + 2 * (int64_t)lo);
-        g[2 * q] = i0 == lo ? make_float2(v.x, v.y) : make_float2(v.z, v.w);
-        g[2 * q + 1] = i1 == lo ? make_float2(v.x, v.y) : make_float2(v.z, v.w);
-      } else {
-        g[2 * q] = *(const float2*)(G + 2 * (int64_t)i0);
-        g[2 * q + 1] = *(const float2*)(G + 2 * (int64_t)i1);
-      }
-    }
-    float ex = 0.0f, ey = 0.0f;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      ex = fmaf(w[b], g[b].x, ex);
-      ey = fmaf(w[b], g[b].y, ey);
-    }
+    sample_pos(R, (k + lane) & (NS - 1), half, inv, p);
+    const bool live = act && occupied(occ, p);
+    float ex = 0.0f, ey = 0.0f;  // a skipped sample's encoding is zero
+    if (__ballot(live) != 0ull) encode_wave(G, N, T, hashed, touch, live, p, odd, ex, ey);
+    if (!act) continue;
     if (a.e_bf16)  // the BF16 MLP reads the encoding rounded to BF16, nothing else
-      ((uint32_t*)a.e)[(int64_t)l * a.S + s] = pack_bf16x2(ex, ey);
+      ((uint32_t*)a.e + at + k)[lane] = pack_bf16x2(ex, ey);
     else
-      a.e[(int64_t)l * a.S + s] = make_float2(ex, ey);
+      (a.e + at + k)[lane] = make_float2(ex, ey);
   }
 }
 
@@ -566,7 +735,6 @@ __device__ inline float rec_value(float x) { return __uint_as_float(__float_as_u
 // L2 (gradient records, read by the next kernel after the whole scatter;
 // parameters and moments after their Adam update): written past the L2's
 // allocation (measured: the accumulation that follows runs 6 % faster).
-typedef float rm_f2v __attribute__((ext_vector_type(2)));
 __device__ inline void nt_store2(float2* p, float2 v) {
   rm_f2v w;
   w[0] = v.x;
@@ -589,6 +757,7 @@ __device__ inline bool bin_records(const StepArgs& a, const ObjStatic& ob, int l
   const uint32_t flags = a.rays[s / NS].flags;
   const float2 g = a.de[(int64_t)l * a.S + s];
   const float half[3] = {ob.half[0], ob.half[1], ob.half[2]};
+  const float inv[3] = {ob.inv2a[0], ob.inv2a[1], ob.inv2a[2]};
   asm volatile("" ::"v"(r0.x), "v"(r1.x), "v"(flags), "v"(g.x), "v"(half[0]), "v"(half[1]),
                "v"(half[2]));
   if (!ray_active(flags)) return false;
@@ -598,7 +767,7 @@ __device__ inline bool bin_records(const StepArgs& a, const ObjStatic& ob, int l
   R.d[0] = r0.w, R.d[1] = r1.x, R.d[2] = r1.y;
   R.tn = r1.z, R.delta = r1.w;
   float p[3];
-  sample_pos(R, (int)(s % NS), half, p);
+  sample_pos(R, (int)(s % NS), half, inv, p);
   make_cell(p, N, cl);
   const uint32_t flip = par ? cell_parity(cl) : 0u;
   cell_corners(cl, N, T, hashed, idx, flip);
@@ -1560,7 +1729,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
           bool live = true;
           if (ob.occ) {
             float p[3];
-            sample_pos(R, i, ob.half, p);
+            sample_pos(R, i, ob.half, ob.inv2a, p);
             live = occupied(ob.occ, p);
           }
           sig[j] = live ? expf(fminf(y0[j], 15.0f)) : 0.0f;
@@ -2295,7 +2464,7 @@ __global__ __launch_bounds__(256) void k_debug_positions(StepArgs a, float* pos)
   if (s >= a.S) return;
   const RayRec R = a.rays[s / NS];
   float p[3] = {0.0f, 0.0f, 0.0f};
-  if (R.flags & RM_F_HIT) sample_pos(R, (int)(s % NS), a.objs[R.obj].half, p);
+  if (R.flags & RM_F_HIT) sample_pos(R, (int)(s % NS), a.objs[R.obj].half, a.objs[R.obj].inv2a, p);
   pos[3 * s] = p[0];
   pos[3 * s + 1] = p[1];
   pos[3 * s + 2] = p[2];
@@ -2352,8 +2521,8 @@ hipError_t rm_launch_raygen(const StepArgs& a, int NS, hipStream_t st) {
 
 hipError_t rm_launch_encode_fwd(const StepArgs& a, int NS, int block, hipStream_t st) {
   if (a.n_bblocks <= 0) return hipSuccess;
-  const int nwg = a.n_bblocks * RM_ENC_SPLIT;  // rounded up to whole rounds of the 8 XCDs
-  RM_NS_SWITCH(NS, (k_encode_fwd<NSC><<<8 * ((nwg + 7) / 8), block, 0, st>>>(a)));
+  // workgroups rounded up to whole rounds of the 8 XCDs
+  RM_NS_SWITCH(NS, (k_encode_fwd<NSC><<<8 * ((a.n_bblocks + 7) / 8), block, 0, st>>>(a)));
   return hipGetLastError();
 }
 

@@ -39,6 +39,14 @@ constexpr int kMaxRaysPerObject = 1 << 22;
 constexpr int64_t kMaxSamplesPerObject = int64_t(1) << 27;
 constexpr int64_t kMaxRaysPerCall = int64_t(1) << 30;
 
+// Threads of a gather workgroup (512 samples) where the autotuner has no say.
+// Up to about 16 rounds of resident workgroups one 64-sample chunk per wave
+// (4096 rays x 64 samples at 16 levels: 162 us the call against 163 with 256
+// threads and 167 with 128); beyond, four, so that a wave's first loads and
+// the chunks without live samples (missing rays, skipped space) cost less
+// (22663 camera rays x 128 samples: 885, 808 and 785 us).
+int gather_block(const StepArgs& a) { return a.n_bblocks > 16384 ? 128 : 512; }
+
 bool ray_count_ok(int rays, int samples_per_ray) {
   return rays > 0 && rays <= kMaxRaysPerObject &&
          (int64_t)rays * samples_per_ray <= kMaxSamplesPerObject;
@@ -266,7 +274,12 @@ ObjStatic to_static(const HostObj& o) {
   s.instance = o.instance;
   s.id = o.id;
   s.n_kf = (int)o.kfs.size();
-  for (int k = 0; k < 3; ++k) s.half[k] = o.box.half[k];
+  bool fast = true;  // div_fixed's range
+  for (int k = 0; k < 3; ++k) {
+    s.half[k] = o.box.half[k];
+    fast = fast && s.half[k] > 0x1p-61f && s.half[k] < 0x1p+59f;
+  }
+  for (int k = 0; k < 3; ++k) s.inv2a[k] = fast ? 1.0f / (s.half[k] + s.half[k]) : 0.0f;
   s.kfs = o.d_kfs;
   s.n_cand = o.n_cand;
   s.occ = o.occ_on ? o.d_occ : nullptr;
@@ -369,6 +382,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       // with at most RM_MERGE_NUM / RM_MERGE_DEN cells per sample along a
       // box's side (on finer levels consecutive samples rarely touch)
       bp.merge = RM_MERGE_DEN * (int)o.N_l[l] <= RM_MERGE_NUM * NS;
+      bp.touch = (int)o.N_l[l] <= 4 * NS;
       // records per region: 8 So / R on average (uniform hash, z-slabs of a
       // dense level); twice that plus a margin, a full bin falls back to atomics
       const int64_t expect = (8 * So + bp.R - 1) / bp.R;
@@ -376,6 +390,12 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       // dense: regions are z-slabs, twice the mean (a full bin falls back to
       // atomics)
       const bool hashed = (o.hashed_mask >> l) & 1u;
+      bp.obj = p.sobj[i].obj;
+      bp.ray_begin = p.sobj[i].ray_begin;
+      bp.N = o.N_l[l];
+      bp.T = o.T_l[l];
+      bp.hashed = hashed;
+      bp.off = o.off[l];
       const int64_t want = hashed ? expect + 8 * (int64_t)std::ceil(std::sqrt((double)expect)) + 256
                                   : 2 * expect + 1024;
       bp.cap = (int)((std::min<int64_t>(want, 8 * So) + 3) & ~(int64_t)3);
@@ -696,7 +716,7 @@ romap_status autotune(romap_ctx* c, const std::vector<std::pair<int, int>>& list
     if (st != ROMAP_OK) return st;
     StepArgs a = plan_args(c, p);
     HIPCHK(c, rm_launch_raygen(a, NS, c->stream));
-    HIPCHK(c, rm_launch_encode_fwd(a, NS, 256, c->stream));
+    HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
     HIPCHK(c, rm_launch_pack(a, K1, c->stream));
     StepArgs ar = a;  // the reduce only sums the records here: no loss, no Adam
     ar.mode = RM_MODE_ADJOINT;
@@ -1548,7 +1568,7 @@ romap_status romap_render(romap_ctx* c, int32_t id, const romap_camera* cam, flo
     a.out_depth = d_depth ? d_depth + p0 : nullptr;
     a.out_tend = d_tend ? d_tend + p0 : nullptr;
     HIPCHK(c, rm_launch_camera_rays(a, NS, M, cc, cam->fx, cam->fy, cam->cx, cam->cy, W, (int)p0, c->stream));
-    HIPCHK(c, rm_launch_encode_fwd(a, NS, 256, c->stream));
+    HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
     HIPCHK(c, rm_launch_pack(a, K1, c->stream));
     HIPCHK(c, rm_launch_field(a, NS, K1, c->cfg.precision, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -2073,7 +2093,7 @@ static romap_status field_common(romap_ctx* c, int32_t id, const float* params_d
   a.params_override = params_dev;
   const int NS = c->cfg.samples_per_ray, L = c->cfg.n_levels, K1 = K1_of(c->cfg);
   HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, c->stream));
-  HIPCHK(c, rm_launch_encode_fwd(a, NS, 256, c->stream));
+  HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
   HIPCHK(c, rm_launch_pack(a, K1, c->stream));
   return ROMAP_OK;
 }
@@ -2168,7 +2188,7 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   a.out_depth = depth_dev;
   a.out_tend = tend_dev;
   HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, c->stream));
-  HIPCHK(c, rm_launch_encode_fwd(a, NS, 256, c->stream));
+  HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
   HIPCHK(c, rm_launch_pack(a, K1, c->stream));
   HIPCHK(c, rm_launch_field(a, NS, K1, c->cfg.precision, c->stream));
   // the host copy of the tables must outlive the transfer
