@@ -40,13 +40,17 @@
 #ifndef RM_SPLIT_SHARE
 #define RM_SPLIT_SHARE 0.50
 #endif
-// The binning merges the corners consecutive samples of a ray share on
-// levels with N_l <= NUM/DEN * samples per ray (NUM/DEN = 2, 4, 8: 1.741,
-// 1.742, 1.746 ms per step on 24 objects; finer levels rarely share any).
-#ifndef RM_MERGE_NUM
-#define RM_MERGE_NUM 4
-#define RM_MERGE_DEN 1
+// The binning merges the corners that consecutive samples of a ray share on
+// dense levels with N_l <= RM_MERGE_DENSE * samples per ray and on hashed ones
+// with N_l <= RM_MERGE_HASHED * samples per ray; finer hashed levels write
+// their corners as x-pairs (8 unmerged corners cost 48 B so, which merging
+// beats only while consecutive cells share corners: 1, 2, 4 -> binning 365, 368,
+// 436 us on 24 objects, 75, 83, 153 us on one of 4096 rays x 64 samples).
+#define RM_MERGE_DENSE 4
+#ifndef RM_MERGE_HASHED
+#define RM_MERGE_HASHED 1
 #endif
+#define RM_PAIR_MAX_RES 2047 /* x-pairs of a level this fine lie in one region of 2^11 entries */
 #define RM_RB_BITS 11       /* binned scatter: table entries per region = 2048 */
 #define RM_RB (1 << RM_RB_BITS)
 #define RM_ACC_WG 512       /* threads of the region accumulation kernel */
@@ -55,12 +59,18 @@
 #endif
 #define RM_ACC_CHUNK 32768  /* records per accumulation workgroup (about; 8192, 16384, 32768: 2.33, 2.23, 2.22 ms per step) */
 #define RM_ACC_MAXK 256     /* accumulation workgroups per region, at most */
-#ifndef RM_GROUP_RECORDS
-#define RM_GROUP_RECORDS (1ll << 29) /* record slots of one bin group (4 GiB) */
+#ifndef RM_GROUP_FLOATS
+#define RM_GROUP_FLOATS (1ll << 30) /* record memory of one bin group, in floats (4 GiB) */
 #endif
-#ifndef RM_ACC_RQ
-#define RM_ACC_RQ 4         /* quads of records per thread the accumulation keeps in registers */
+#ifndef RM_ACC_CORNERS
+#define RM_ACC_CORNERS 16   /* corner records per thread the accumulation keeps in registers */
 #endif
+#ifndef RM_ACC_PAIRS
+#define RM_ACC_PAIRS 8      /* the same of pair records */
+#endif
+#define RM_STAGE_BYTES 32768 /* LDS staging of the binning kernel: all 4 pair records per sample, */
+#define RM_STAGE_CORNERS 2728 /* or this many corner records (12 B each with their slot) */
+static_assert(RM_SCAT_WG * 4 * 16 <= RM_STAGE_BYTES && RM_STAGE_CORNERS * 12 <= RM_STAGE_BYTES, "staging");
 #define RM_FX_BITS 38       /* fixed-point fraction bits of the region sums */
 #define RM_MAX_REGIONS 8192 /* 2^24 / 2^11 */
 
@@ -165,10 +175,11 @@ struct BinPair {        // one (object of the launch, binned level)
   int32_t so, l;
   int32_t nb;           // sample blocks of RM_SCAT_WG of the object
   int32_t R;            // regions of the level's table
-  int64_t rec_base;     // first record slot of this pair
+  int64_t rec_base;     // the pair's records: first float of the record memory
   int32_t bin_base;     // first bin (region) of this pair
   int32_t cap;          // record slots per bin (multiple of 4)
   int32_t K;            // accumulation workgroups per bin
+  int32_t pairs;        // records are x-pairs of corners (12 B), else corners (8 B)
   int32_t merge;        // corners shared by consecutive samples of a ray are merged
   int32_t touch;        // consecutive samples often share corners: gathered in parity slots
   int32_t obj, ray_begin; // the object, its first ray in the launch
@@ -187,8 +198,8 @@ struct Bin {            // one accumulation workgroup: chunk k of K of one regio
   int32_t pair, region, k, pad;
 };
 
-// Pairs are binned and accumulated in groups of at most RM_GROUP_RECORDS
-// record slots, reused from group to group, which bounds the record memory
+// Pairs are binned and accumulated in groups of at most RM_GROUP_FLOATS of
+// record memory, reused from group to group, which bounds the record memory
 // of very large launches.  (Groups small enough to keep the records in the
 // last-level cache were measured slower: each launch then ends in a partial
 // wave of workgroups.)
@@ -244,7 +255,7 @@ struct StepArgs {
   int32_t n_regions;    // bins over all pairs
   int32_t bin_max_R;    // most regions of one pair
   int32_t* bin_count;   // records per bin (zeroed by the gather kernel)
-  float2* rec_val;      // records: values with the entry index in their low mantissa bits
+  float* rec;           // gradient records (corner or pair records, by level)
 };
 
 // Launch helpers implemented in romap_kernels.hip.

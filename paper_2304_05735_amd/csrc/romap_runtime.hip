@@ -92,7 +92,7 @@ struct Plan {                 // one launch: its objects, rays and work lists
   std::vector<BinBlock> bblocks;
   std::vector<Bin> bins;
   std::vector<BinGroup> bgroups;
-  int64_t rec_size = 0;      // record slots of the largest group
+  int64_t rec_size = 0;      // record memory of the largest group (floats)
   int64_t bin_regions = 0;  // regions over all pairs (bin_count entries)
   int n_rays = 0;
   int64_t S = 0;
@@ -164,8 +164,8 @@ struct romap_ctx {
   size_t cap_tables = 0;
   int32_t* d_bin_count = nullptr;
   size_t cap_bin_count = 0;
-  float2* d_rec_val = nullptr;
-  size_t cap_rec_val = 0;
+  float* d_rec = nullptr;
+  size_t cap_rec = 0;
   // graph of the last batched step
   hipGraphExec_t gexec = nullptr;
   std::vector<int64_t> gsig;
@@ -313,7 +313,7 @@ StepArgs base_args(romap_ctx* c) {
   a.rays = c->d_rays;
   a.e = c->d_e;
   a.bin_count = c->d_bin_count;
-  a.rec_val = c->d_rec_val;
+  a.rec = c->d_rec;
   a.de = c->d_de;
   a.partials = c->d_partials;
   a.wpack32 = c->d_wpack32;
@@ -368,7 +368,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
   build_items(p);
   // binned gradient scatter: every (object, level) pair
   const int NS = c->cfg.samples_per_ray;
-  int64_t grp_rec = 0;  // record slots of the open group
+  int64_t grp_rec = 0;  // record memory of the open group (floats)
   for (size_t i = 0; i < p.sobj.size(); ++i) {
     const HostObj& o = c->objs[p.sobj[i].obj];
     const int64_t So = (int64_t)p.sobj[i].n_rays * NS;
@@ -378,17 +378,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       bp.l = l;
       bp.nb = (int)((So + RM_SCAT_WG - 1) / RM_SCAT_WG);
       bp.R = (int)((o.T_l[l] + RM_RB - 1) >> RM_RB_BITS);
-      // corners shared by consecutive samples of a ray are merged on levels
-      // with at most RM_MERGE_NUM / RM_MERGE_DEN cells per sample along a
-      // box's side (on finer levels consecutive samples rarely touch)
-      bp.merge = RM_MERGE_DEN * (int)o.N_l[l] <= RM_MERGE_NUM * NS;
       bp.touch = (int)o.N_l[l] <= 4 * NS;
-      // records per region: 8 So / R on average (uniform hash, z-slabs of a
-      // dense level); twice that plus a margin, a full bin falls back to atomics
-      const int64_t expect = (8 * So + bp.R - 1) / bp.R;
-      // hashed: near-uniform counts, the mean plus 8 standard deviations;
-      // dense: regions are z-slabs, twice the mean (a full bin falls back to
-      // atomics)
       const bool hashed = (o.hashed_mask >> l) & 1u;
       bp.obj = p.sobj[i].obj;
       bp.ray_begin = p.sobj[i].ray_begin;
@@ -396,22 +386,35 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       bp.T = o.T_l[l];
       bp.hashed = hashed;
       bp.off = o.off[l];
+      // Corners shared by consecutive samples of a ray are merged on coarse
+      // levels; on finer hashed ones x-pairs of corners are the records, half
+      // as many at 3/4 of the bytes (a level as fine as a whole region keeps
+      // corner records: a pair may straddle two regions).
+      bp.merge = (int)o.N_l[l] <= (hashed ? RM_MERGE_HASHED : RM_MERGE_DENSE) * NS;
+      bp.pairs = hashed && !bp.merge && (int)o.N_l[l] <= RM_PAIR_MAX_RES;
+      // records per region: per_sample So / R on average (uniform hash, z-slabs
+      // of a dense level); hashed: near-uniform counts, the mean plus 8
+      // standard deviations; dense: twice the mean (a full bin falls back to
+      // atomics)
+      const int64_t all = (bp.pairs ? 4 : 8) * So;
+      const int64_t expect = (all + bp.R - 1) / bp.R;
       const int64_t want = hashed ? expect + 8 * (int64_t)std::ceil(std::sqrt((double)expect)) + 256
                                   : 2 * expect + 1024;
-      bp.cap = (int)((std::min<int64_t>(want, 8 * So) + 3) & ~(int64_t)3);
+      bp.cap = (int)((std::min<int64_t>(want, all) + 3) & ~(int64_t)3);
       if (c->debug_bin_cap > 0) bp.cap = std::min(bp.cap, (c->debug_bin_cap + 3) & ~3);
-      // workgroups per region: about RM_ACC_CHUNK records each, and at most
-      // 2^(62 - RM_FX_BITS) / 2 per workgroup so no fixed-point sum can overflow
+      // workgroups per region: about RM_ACC_CHUNK corners each, and at most
+      // 2^(62 - RM_FX_BITS) / 2 records per workgroup so no fixed-point sum can overflow
       const int64_t kmin = (bp.cap + ((int64_t)1 << (61 - RM_FX_BITS)) - 1) >> (61 - RM_FX_BITS);
-      bp.K = (int)std::max<int64_t>(kmin, std::min<int64_t>(RM_ACC_MAXK, expect / RM_ACC_CHUNK));
+      bp.K = (int)std::max<int64_t>(kmin, std::min<int64_t>(RM_ACC_MAXK,
+                                                            (8 * So + bp.R - 1) / bp.R / RM_ACC_CHUNK));
       bp.K = std::max(bp.K, 1);
-      const int64_t slots = (int64_t)bp.R * bp.cap;
-      if (p.bgroups.empty() || (grp_rec > 0 && grp_rec + slots > RM_GROUP_RECORDS)) {
+      const int64_t slots = (int64_t)bp.R * bp.cap * (bp.pairs ? 3 : 2);  // floats
+      if (p.bgroups.empty() || (grp_rec > 0 && grp_rec + slots > RM_GROUP_FLOATS)) {
         const int nbb = (int)p.bblocks.size(), nbin = (int)p.bins.size();
         p.bgroups.push_back(BinGroup{nbb, nbb, nbin, nbin});
         grp_rec = 0;
       }
-      bp.rec_base = grp_rec;  // record slots are reused from group to group
+      bp.rec_base = grp_rec;  // record memory is reused from group to group
       grp_rec += slots;
       p.rec_size = std::max(p.rec_size, grp_rec);
       bp.bin_base = (int)p.bin_regions;
@@ -499,7 +502,7 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
   HIPALLOC(c, regrow(&c->d_wpack16, &c->cap_w16, std::max<size_t>(max_sobj * RM_WPACK_NH(nh), 1)));
   HIPALLOC(c, regrow(&c->d_tables, &c->cap_tables, std::max<size_t>(tab, 256)));
   HIPALLOC(c, regrow(&c->d_bin_count, &c->cap_bin_count, std::max<size_t>(max_bins, 1)));
-  HIPALLOC(c, regrow(&c->d_rec_val, &c->cap_rec_val, std::max<size_t>(max_rec, 1)));
+  HIPALLOC(c, regrow(&c->d_rec, &c->cap_rec, std::max<size_t>(max_rec, 1)));
   std::vector<char> h(tab);
   for (Plan* p : plans) {
     if (!p->sobj.empty()) std::memcpy(h.data() + p->off_sobj, p->sobj.data(), p->sobj.size() * sizeof(StepObj));
@@ -537,7 +540,7 @@ StepArgs plan_args(romap_ctx* c, const Plan& p) {
   a.wpack32 = c->d_wpack32 + p.so_wpack;
   a.wpack16 = c->d_wpack16 + p.so_wpack;
   a.bin_count = c->d_bin_count + p.so_bins;
-  a.rec_val = c->d_rec_val + p.so_rec;
+  a.rec = c->d_rec + p.so_rec;
   a.n_regions = (int)p.bin_regions;
   a.bin_max_R = 0;
   for (const BinPair& bp : p.bpairs) a.bin_max_R = std::max(a.bin_max_R, bp.R);
@@ -652,7 +655,8 @@ void split_list(romap_ctx* c, const std::vector<std::pair<int, int>>& list,
 }
 
 // Adds the gradient records the step just run wrote into its bins (the
-// binning kernel's fill counters, clamped at each bin's capacity).
+// binning kernel's fill counters, clamped at each bin's capacity), in units
+// of 8 B.
 romap_status count_records(romap_ctx* c, const Plan& p) {
   if (p.bin_regions == 0) return ROMAP_OK;
   std::vector<int32_t> cnt((size_t)p.bin_regions);
@@ -660,7 +664,8 @@ romap_status count_records(romap_ctx* c, const Plan& p) {
                            hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   for (const BinPair& bp : p.bpairs)
-    for (int r = 0; r < bp.R; ++r) c->records_sum += std::min(cnt[bp.bin_base + r], bp.cap);
+    for (int r = 0; r < bp.R; ++r)
+      c->records_sum += (bp.pairs ? 1.5 : 1.0) * std::min(cnt[bp.bin_base + r], bp.cap);
   return ROMAP_OK;
 }
 
@@ -972,7 +977,7 @@ romap_status romap_destroy(romap_ctx* c) {
   hipFree(c->d_mcnt);
   hipFree(c->d_mbsum);
   hipFree(c->d_mtris);
-  hipFree(c->d_rec_val);
+  hipFree(c->d_rec);
   if (c->own_stream) hipStreamDestroy(c->stream);
   delete c;
   return ROMAP_OK;
@@ -2181,7 +2186,7 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   a.wpack16 = (uint16_t*)(base + o_w16);
   a.de = nullptr;  // the forward writes no adjoints, records or partial sums
   a.partials = nullptr;
-  a.rec_val = nullptr;
+  a.rec = nullptr;
   a.params_override = params_dev;
   a.mode = RM_MODE_FORWARD;
   a.out_rgb = rgb_dev;
