@@ -1701,41 +1701,47 @@ __device__ inline void load_e_b(const uint32_t* e, int64_t S, int64_t s, int L, 
 
 // NH: hidden layers of the density MLP (1, or 2 and 3 for the model-size
 // study); the deeper variants run one wave per SIMD (their 64 x 64 weight
-// gradients are accumulated in registers), and their work-item record shares
-// LDS with the weights, which are no longer read when it is written.
-template <int PREC, int NS, int K1, int NH>
+// gradients are accumulated in registers).  The work-item record shares LDS
+// with the weights, which are no longer read when it is written, and a layer's
+// two staged tiles follow each other, so that two FP32 workgroups fit a CU
+// (one before: 97 KB; 4096 rays x 64 samples 138 -> 112 us).
+// FWD: colour, depth and T_end only (RM_MODE_FORWARD): without the backward
+// half's registers and operands several waves share a SIMD and hide the
+// layers' latency (the same rays: FP32 44 -> 32 us).
+template <int PREC, int NS, int K1, int NH, bool FWD>
 #ifndef RM_FIELD_BF16_WAVES
 #define RM_FIELD_BF16_WAVES 2
 #endif
-__global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 1 : (PREC == 1 ? RM_FIELD_BF16_WAVES : 2)))) void k_field(StepArgs a) {
+__global__ __launch_bounds__(RM_WG) __attribute__((
+    amdgpu_waves_per_eu(FWD ? (PREC == 0 && K1 == 32 ? 3 : NH > 2 ? 2 : NH > 1 ? 3 : 4) : NH > 1 ? 1 : (PREC == 1 ? RM_FIELD_BF16_WAVES : 2)))) void k_field(StepArgs a) {
   typedef Mma<PREC> MM;
   typedef typename MM::wtype wt;
   constexpr int NB = NS / 16;             // 16-sample blocks per ray
   constexpr int SPL = NS > 64 ? NS / 64 : 1;  // samples per lane in the composite
-  constexpr int STG = 64 * MM::STRIDE;    // one staging tile (64 feature rows)
+  // staged rows of a wave: a layer's adjoint and input (64 + K1, 64 + 16, or
+  // 64 + 64 of a hidden-to-hidden layer)
+  constexpr int ROWS = NH > 1 ? 128 : 64 + K1;
   constexpr int KQ = K1 / 16;
   // a ray's encodings stay in registers from the forward to the backward
   // pass when they fit (NS <= 64, one hidden layer), else the backward reads
   // them again
-  constexpr bool KEEP_E = NH == 1 && NB * KQ <= 8 && (PREC == 0 || RM_FIELD_BF16_WAVES < 3);
+  constexpr bool KEEP_E = !FWD && NH == 1 && NB * KQ <= 8 && (PREC == 0 || RM_FIELD_BF16_WAVES < 3);
   constexpr int NBK = KEEP_E ? NB : 1;
   constexpr int WP = RM_WPACK_NH(NH);
+  // a forward pass of one hidden layer needs the forward operands only
+  constexpr int WUSED = FWD && NH == 1 ? RM_OFF_B4 : WP;
   constexpr int RL = RM_REC_LOSS_NH(NH);
-  constexpr int WBYTES = WP * (int)sizeof(wt), RBYTES = (RL + 1) * 4;
-  // the work-item record shares LDS with the weights, which are no longer
-  // read when it is written (fewer bytes per workgroup, more workgroups per CU)
-  constexpr bool ALIAS = NH > 1 || PREC == 1;
+  constexpr int WBYTES = WUSED * (int)sizeof(wt), RBYTES = FWD ? 0 : (RL + 1) * 4;
   // BF16 with one hidden layer: activations kept as rounded BF16 pairs
   constexpr bool PACKED = PREC == 1 && NH == 1;
 
-  __shared__ __align__(16) char s_wraw[ALIAS && RBYTES > WBYTES ? RBYTES : WBYTES];
+  __shared__ __align__(16) char s_wraw[RBYTES > WBYTES ? RBYTES : WBYTES];
   // BF16 with one hidden layer stages tiles of 32 samples (pairs of blocks)
-  constexpr int STGS = PACKED ? 64 * Mma<1>::STRIDE2 : STG;
-  __shared__ __align__(16) wt s_stage[4][2][STGS];
+  constexpr int STR = PACKED ? Mma<1>::STRIDE2 : MM::STRIDE;
+  __shared__ __align__(16) wt s_stage[4][FWD ? 8 : ROWS * STR];
   __shared__ __align__(16) float s_rv[4][NS * 4];
-  __shared__ float s_rec_own[ALIAS ? 1 : RL + 1];
   wt* s_w = (wt*)s_wraw;
-  float* s_rec = ALIAS ? (float*)s_wraw : s_rec_own;
+  float* s_rec = (float*)s_wraw;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, n = lane & 15;
@@ -1751,7 +1757,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
     const uint4* src = (const uint4*)((PREC ? (const void*)(a.wpack16 + (int64_t)it.so * WP)
                                             : (const void*)(a.wpack32 + (int64_t)it.so * WP)));
     uint4* dst = (uint4*)s_w;
-    constexpr int NV = WP * (int)sizeof(wt) / 16;
+    constexpr int NV = WBYTES / 16;
     for (int j = tid; j < NV; j += RM_WG) dst[j] = src[j];
   }
   __syncthreads();
@@ -1764,8 +1770,9 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
   const wt* wB3 = s_w + RM_OFF_B3;
   const wt* wB2 = s_w + RM_OFF_B2;
   const wt* wB1 = s_w + RM_OFF_B1;
-  wt* gbuf = s_stage[wave][0];
-  wt* xbuf = s_stage[wave][1];
+  wt* gbuf = s_stage[wave];           // a layer's adjoint, then its input
+  wt* x16 = gbuf + 16 * STR;          // after an adjoint of 16 rows
+  wt* x64 = gbuf + 64 * STR;          // after one of 64
   float* rv = s_rv[wave];
   // encodings: FP32 fragments, or with the BF16 MLP the stored BF16 pairs as
   // they are (the MLP reads nothing else of them)
@@ -1803,7 +1810,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
     const int ray = __builtin_amdgcn_readfirstlane(it.ray_begin + rr);
     const RayRec R = a.rays[ray];
     if (!ray_active(R.flags)) {
-      if (mode == RM_MODE_FORWARD && lane == 0) {
+      if (FWD && lane == 0) {
         if (a.out_rgb) a.out_rgb[3 * ray] = a.out_rgb[3 * ray + 1] = a.out_rgb[3 * ray + 2] = 0.0f;
         if (a.out_depth) a.out_depth[ray] = 0.0f;
         if (a.out_tend) a.out_tend[ray] = 1.0f;
@@ -1920,7 +1927,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
       const float Stot = wave_sum(lane_tau);
       const float Tend = expf(-Stot);
 
-      if (mode == RM_MODE_FORWARD) {
+      if constexpr (FWD) {
         if (lane == 0) {
           if (a.out_rgb) {
             a.out_rgb[3 * ray] = Ch[0];
@@ -1931,8 +1938,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
           if (a.out_tend) a.out_tend[ray] = Tend;
         }
         continue;
-      }
-
+      } else {
       float gC[3], gD = 0.0f, gT = 0.0f, dens = 0.0f;
       if (mode == RM_MODE_TRAIN) {
         // Eq. 7-11: squared colour error against the image (object rays) or
@@ -1990,7 +1996,9 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
           for (int k = 0; k < 3; ++k) q[1 + k] = w[j] * gC[k] * c[j][k] * sigmoidf_(-zc[j][k]);
         }
       }
+      }
     }
+    if constexpr (!FWD) {
     wave_lds_sync();
 
     // ---- backward: recompute activations per block, adjoints, dW ----
@@ -2036,10 +2044,10 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           MM::stage_b2(gbuf, dZb[h], 1, lane, 16 * h);
-          MM::stage_b2(xbuf, H2b[h], 4, lane, 16 * h);
+          MM::stage_b2(x16, H2b[h], 4, lane, 16 * h);
         }
         wave_lds_sync();
-        MM::template dw32<16, 64>(gbuf, xbuf, acc4, lane);
+        MM::template dw32<16, 64>(gbuf, x16, acc4, lane);
         wave_lds_sync();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -2052,10 +2060,10 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           MM::stage_b2(gbuf, dH2b[h], 4, lane, 16 * h);
-          MM::stage_b2(xbuf, Yb[h], 1, lane, 16 * h);
+          MM::stage_b2(x64, Yb[h], 1, lane, 16 * h);
         }
         wave_lds_sync();
-        MM::template dw32<64, 16>(gbuf, xbuf, acc3, lane);
+        MM::template dw32<64, 16>(gbuf, x64, acc3, lane);
         wave_lds_sync();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -2068,10 +2076,10 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           MM::stage_b2(gbuf, dYb[h], 1, lane, 16 * h);
-          MM::stage_b2(xbuf, H1b[h], 4, lane, 16 * h);
+          MM::stage_b2(x16, H1b[h], 4, lane, 16 * h);
         }
         wave_lds_sync();
-        MM::template dw32<16, 64>(gbuf, xbuf, acc2, lane);
+        MM::template dw32<16, 64>(gbuf, x16, acc2, lane);
         wave_lds_sync();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -2084,10 +2092,10 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           MM::stage_b2(gbuf, dH1b[h], 4, lane, 16 * h);
-          MM::stage_b2(xbuf, E2[h], KQ, lane, 16 * h);
+          MM::stage_b2(x64, E2[h], KQ, lane, 16 * h);
         }
         wave_lds_sync();
-        MM::template dw32<64, K1>(gbuf, xbuf, acc1, lane);
+        MM::template dw32<64, K1>(gbuf, x64, acc1, lane);
         wave_lds_sync();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -2137,9 +2145,9 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
       }
       // colour head: dW4 += dZ^T H2, dH2 = W4^T dZ masked by ReLU
       MM::stage(gbuf, dZ, 1, lane);
-      MM::stage(xbuf, H2, 4, lane);
+      MM::stage(x16, H2, 4, lane);
       wave_lds_sync();
-      MM::template dw<16, 64>(gbuf, xbuf, acc4, lane);
+      MM::template dw<16, 64>(gbuf, x16, acc4, lane);
       wave_lds_sync();
       MM::template gemm<64, 16>(wB4, dZ, dH2, lane);
 #pragma unroll
@@ -2148,17 +2156,17 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
         for (int r = 0; r < 4; ++r) dH2[f][r] = H2[f][r] > 0.0f ? dH2[f][r] : 0.0f;
       // dW3 += dH2^T Y, dY = W3^T dH2 (+ density adjoint in row 0)
       MM::stage(gbuf, dH2, 4, lane);
-      MM::stage(xbuf, Y, 1, lane);
+      MM::stage(x64, Y, 1, lane);
       wave_lds_sync();
-      MM::template dw<64, 16>(gbuf, xbuf, acc3, lane);
+      MM::template dw<64, 16>(gbuf, x64, acc3, lane);
       wave_lds_sync();
       MM::template gemm<16, 64>(wB3, dH2, dY, lane);
       if (g == 0) dY[0][0] += dy0;
       // dW2 += dY^T H1, dH1 = W2^T dY masked
       MM::stage(gbuf, dY, 1, lane);
-      MM::stage(xbuf, H1, 4, lane);
+      MM::stage(x16, H1, 4, lane);
       wave_lds_sync();
-      MM::template dw<16, 64>(gbuf, xbuf, acc2, lane);
+      MM::template dw<16, 64>(gbuf, x16, acc2, lane);
       wave_lds_sync();
       MM::template gemm<64, 16>(wB2, dY, dH1, lane);
 #pragma unroll
@@ -2170,9 +2178,9 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
 #pragma unroll
       for (int k = NH - 1; k >= 1; --k) {
         MM::stage(gbuf, dH1, 4, lane);
-        MM::stage(xbuf, HH[k - 1], 4, lane);
+        MM::stage(x64, HH[k - 1], 4, lane);
         wave_lds_sync();
-        MM::template dw<64, 64>(gbuf, xbuf, accH[k - 1], lane);
+        MM::template dw<64, 64>(gbuf, x64, accH[k - 1], lane);
         wave_lds_sync();
         floatx4 dP[4];
         MM::template gemm<64, 64>(s_w + RM_OFF_HB(k), dH1, dP, lane);
@@ -2184,11 +2192,11 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
       // dW1 += dH^T E, dE = W1^T dH  (dH of the first hidden layer)
       MM::stage(gbuf, dH1, 4, lane);
       if constexpr (PREC == 1)
-        MM::stage_b(xbuf, E, KQ, lane);
+        MM::stage_b(x64, E, KQ, lane);
       else
-        MM::stage(xbuf, E, KQ, lane);
+        MM::stage(x64, E, KQ, lane);
       wave_lds_sync();
-      MM::template dw<64, K1>(gbuf, xbuf, acc1, lane);
+      MM::template dw<64, K1>(gbuf, x64, acc1, lane);
       wave_lds_sync();
       MM::template gemm<K1, 64>(wB1, dH1, dE, lane);
 #pragma unroll
@@ -2198,6 +2206,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
         if (l1 < L) a.de[(int64_t)l1 * S + s] = make_float2(dE[q][2], dE[q][3]);
       }
     }
+    }
   }
 
   // ---- work-item record: weight gradients in parameter order, and loss ----
@@ -2205,10 +2214,10 @@ __global__ __launch_bounds__(RM_WG) __attribute__((amdgpu_waves_per_eu(NH > 1 ? 
   // add), with plain LDS accesses: each wave covers every record entry once,
   // and float atomics in LDS are slow.  The order is fixed, so the record is
   // deterministic.
-  if (mode != RM_MODE_FORWARD) {
+  if constexpr (!FWD) {
     const int oh = RM_HIDDEN * din, o2 = oh + (NH - 1) * RM_HH, o3 = o2 + RM_DOUT * RM_HIDDEN,
               o4 = o3 + RM_HIDDEN * RM_GEO;
-    if (ALIAS) __syncthreads();  // the record overwrites the weights: every wave is done
+    __syncthreads();  // the record overwrites the weights: every wave is done
     for (int turn = 0; turn < RM_WG / 64; ++turn) {
       if (wave == turn) {
         const bool first = turn == 0;
@@ -2712,7 +2721,11 @@ hipError_t rm_launch_pack(const StepArgs& a, int K1, hipStream_t st) {
 
 template <int PREC, int K1, int NH>
 static hipError_t launch_field_k(const StepArgs& a, int NS, hipStream_t st) {
-  RM_NS_SWITCH(NS, (k_field<PREC, NSC, K1, NH><<<a.n_items, RM_WG, 0, st>>>(a)));
+  if (a.mode == RM_MODE_FORWARD) {
+    RM_NS_SWITCH(NS, (k_field<PREC, NSC, K1, NH, true><<<a.n_items, RM_WG, 0, st>>>(a)));
+  } else {
+    RM_NS_SWITCH(NS, (k_field<PREC, NSC, K1, NH, false><<<a.n_items, RM_WG, 0, st>>>(a)));
+  }
   return hipGetLastError();
 }
 
