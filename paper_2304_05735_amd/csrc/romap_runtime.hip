@@ -369,10 +369,29 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
   // binned gradient scatter: every (object, level) pair
   const int NS = c->cfg.samples_per_ray;
   int64_t grp_rec = 0;  // record memory of the open group (floats)
+  std::vector<int> grp_pairs;  // its pairs
+  // The accumulation's workgroups go over a group's regions object by object
+  // and level by level (in the pairs' order, coarse and fine in turn, one
+  // object of 1999 rays x 128 samples took 82 us against 54).
+  auto close_group = [&]() {
+    std::sort(grp_pairs.begin(), grp_pairs.end(), [&](int x, int y) {
+      const BinPair &u = p.bpairs[x], &v = p.bpairs[y];
+      return u.so != v.so ? u.so < v.so : u.l < v.l;
+    });
+    for (int pi : grp_pairs)
+      for (int r = 0; r < p.bpairs[pi].R; ++r)
+        for (int k = 0; k < p.bpairs[pi].K; ++k) p.bins.push_back(Bin{pi, r, k, 0});
+    if (!p.bgroups.empty()) p.bgroups.back().bin_end = (int)p.bins.size();
+    grp_pairs.clear();
+  };
   for (size_t i = 0; i < p.sobj.size(); ++i) {
     const HostObj& o = c->objs[p.sobj[i].obj];
     const int64_t So = (int64_t)p.sobj[i].n_rays * NS;
-    for (int l = 0; l < o.L; ++l) {
+    // Levels coarse and fine in turn: the gather and the binning give each XCD
+    // a contiguous range of blocks, and a fine level costs three times a
+    // coarse one (4096 rays x 64 samples: gather 87 -> 71 us, binning 78 -> 72).
+    for (int li = 0; li < o.L; ++li) {
+      const int l = (li & 1) ? o.L - 1 - li / 2 : li / 2;
       BinPair bp{};
       bp.so = (int)i;
       bp.l = l;
@@ -410,7 +429,9 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       bp.K = std::max(bp.K, 1);
       const int64_t slots = (int64_t)bp.R * bp.cap * (bp.pairs ? 3 : 2);  // floats
       if (p.bgroups.empty() || (grp_rec > 0 && grp_rec + slots > RM_GROUP_FLOATS)) {
-        const int nbb = (int)p.bblocks.size(), nbin = (int)p.bins.size();
+        const int nbb = (int)p.bblocks.size();
+        close_group();
+        const int nbin = (int)p.bins.size();
         p.bgroups.push_back(BinGroup{nbb, nbb, nbin, nbin});
         grp_rec = 0;
       }
@@ -424,17 +445,16 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       const int pi = (int)p.bpairs.size();
       p.bpairs.push_back(bp);
       for (int b = 0; b < bp.nb; ++b) p.bblocks.push_back(BinBlock{pi, b});
-      for (int r = 0; r < bp.R; ++r)
-        for (int k = 0; k < bp.K; ++k) p.bins.push_back(Bin{pi, r, k, 0});
       if (bp.K > 1)
         for (int r = 0; r < bp.R; ++r) {
           const int64_t ne = std::min<int64_t>(RM_RB, (int64_t)o.T_l[l] - (int64_t)r * RM_RB);
           for (int sub = 0; sub * RM_FIN_WG < ne; ++sub) p.fins.push_back(Fin{pi, r, sub, 0});
         }
       p.bgroups.back().bb_end = (int)p.bblocks.size();
-      p.bgroups.back().bin_end = (int)p.bins.size();
+      grp_pairs.push_back(pi);
     }
   }
+  close_group();
 }
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
