@@ -368,9 +368,10 @@ romap_status romap_field_forward_noalloc(romap_ctx* ctx, int32_t object_id,
                                          float* tend_dev);
 
 /* Kernels of one training step, in launch order. */
-#define ROMAP_PHASE_RAYGEN 0      /* ray draw, classification, box clipping (Sec. V-B) */
-#define ROMAP_PHASE_ENCODE 1      /* hash-grid gather */
-#define ROMAP_PHASE_PACK 2        /* MLP weights -> MFMA operand images, step advance */
+#define ROMAP_PHASE_RAYGEN 0      /* ray draw, classification, box clipping (Sec. V-B); MLP
+                                     weights -> MFMA operand images */
+#define ROMAP_PHASE_ENCODE 1      /* hash-grid gather; step advance */
+#define ROMAP_PHASE_PACK 2        /* no kernel of its own (part of RAYGEN): always 0 */
 #define ROMAP_PHASE_FIELD 3       /* MLP, volume rendering, loss, adjoint */
 #define ROMAP_PHASE_REDUCE 4      /* per-object MLP gradient and loss; Adam on the MLP */
 #define ROMAP_PHASE_BIN_SCATTER 5 /* hash-grid gradient: records sorted into bins */

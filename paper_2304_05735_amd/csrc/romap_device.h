@@ -259,18 +259,19 @@ struct StepArgs {
 };
 
 // Launch helpers implemented in romap_kernels.hip.
-hipError_t rm_launch_raygen(const StepArgs& a, int NS, hipStream_t st);
+// The ray kernels also pack the MLP weights of the launch's objects (K1 = 0: no).
+hipError_t rm_launch_raygen(const StepArgs& a, int NS, int K1, hipStream_t st);
 hipError_t rm_launch_encode_fwd(const StepArgs& a, int NS, int block, hipStream_t st);
 hipError_t rm_launch_bin_scatter(const StepArgs& a, const BinGroup& g, int NS, hipStream_t st);
 hipError_t rm_launch_bin_acc(const StepArgs& a, const BinGroup& g, hipStream_t st);
-hipError_t rm_launch_pack(const StepArgs& a, int K1, hipStream_t st);
 hipError_t rm_launch_field(const StepArgs& a, int NS, int K1, int prec, hipStream_t st);
 hipError_t rm_launch_reduce(const StepArgs& a, hipStream_t st);
 hipError_t rm_launch_bin_finish(const StepArgs& a, hipStream_t st);
 hipError_t rm_launch_camera_rays(const StepArgs& a, int NS, const float* M, const float* c,
                                  float fx, float fy, float cx, float cy, int W, int pix0,
-                                 hipStream_t st);
-hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, hipStream_t st);
+                                 int K1, hipStream_t st);
+hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, int K1,
+                               hipStream_t st);
 // marching cubes over a (res+1)^3 corner grid (x fastest)
 #define RM_MC_SCAN 1024      /* cells per block of the count scan */
 #define RM_MC_MAX_RES 160    /* res^3 <= 4096 scan blocks of RM_MC_SCAN */

@@ -4,11 +4,10 @@
 // One step over every object of a launch:
 //   k_raygen       draw rays in each object's detection boxes, classify them by
 //                  the instance mask, back-project into the object frame, clip
-//                  to the 3D box (Sec. V-B)                        [FP32, exact]
+//                  to the 3D box (Sec. V-B)                        [FP32, exact];
+//                  MLP weights -> MFMA operand images (FP32 and BF16)
 //   k_encode_fwd   multiresolution hash-grid gather, one (object, level) table
-//                  at a time
-//   k_pack         MLP weights -> MFMA operand images (FP32 and BF16); advances
-//                  the Adam step
+//                  at a time; advances the Adam step
 //   k_field        fused per-ray MLP (MFMA) + volume rendering (Eq. 6) + loss
 //                  (Eq. 7-11) + adjoint, activations recomputed in the backward
 //                  half, wavefront prefix scans for transmittance
@@ -405,9 +404,85 @@ __device__ inline void pixel_ray(const float* M, const float* c, float fx, float
 }
 
 // ---------------------------------------------------------------------------
+// MLP weights -> MFMA operand images.  For a GEMM Out(M x 16 samples) =
+// A(M x K) X(K x 16), operand element (t, q, r, lane) is
+// A[16t + lane%16][16q + 4(lane/16) + r]; the FP32 image orders it
+// ((t Q + q) 4 + r) 64 + lane (one 16x16x4 operand per 64 contiguous values),
+// the BF16 image ((t Q + q) 64 + lane) 4 + r (one 16x16x16 operand per lane)
+// when K = 16, and for K a multiple of 32 ((t C + c) 64 + lane) 8 + q8 with
+// A[16t + lane%16][32c + (q8 < 4 ? 4g + q8 : 16 + 4g + q8 - 4)], g = lane/16
+// (one 16x16x32 operand per lane, in the slot order of Mma<1>).
+// Operands 8 + 2(k-1) and 9 + 2(k-1) are the k-th hidden-to-hidden matrix of
+// a deeper density MLP (nh hidden layers) and its transpose.
+__device__ inline float mlp_A(const float* W, int din, int nh, int gemm, int m, int k) {
+  const float* W1 = W;
+  const float* Wh = W1 + RM_HIDDEN * din;
+  const float* W2 = Wh + (nh - 1) * RM_HH;
+  const float* W3 = W2 + RM_DOUT * RM_HIDDEN;
+  const float* W4 = W3 + RM_HIDDEN * RM_GEO;
+  switch (gemm) {
+    case 0: return k < din ? W1[m * din + k] : 0.0f;                 // F1 64 x K1
+    case 1: return W2[m * RM_HIDDEN + k];                             // F2 16 x 64
+    case 2: return k >= 1 ? W3[m * RM_GEO + (k - 1)] : 0.0f;          // F3 64 x 16
+    case 3: return m < 3 ? W4[m * RM_HIDDEN + k] : 0.0f;              // F4 16 x 64
+    case 4: return k < 3 ? W4[k * RM_HIDDEN + m] : 0.0f;              // B4 64 x 16
+    case 5: return m >= 1 ? W3[k * RM_GEO + (m - 1)] : 0.0f;          // B3 16 x 64
+    case 6: return W2[k * RM_HIDDEN + m];                             // B2 64 x 16
+    case 7: return m < din ? W1[k * din + m] : 0.0f;                  // B1 K1 x 64
+    default: {
+      const float* H = Wh + ((gemm - 8) >> 1) * RM_HH;
+      return (gemm & 1) ? H[k * RM_HIDDEN + m] : H[m * RM_HIDDEN + k];  // Wh_k^T, Wh_k
+    }
+  }
+}
+
+// Work item j of the packing: operand j % P of object j / P of the launch, in
+// RM_PACK_SPLIT parts.  Run by the workgroups of the ray kernels past those of
+// the rays (the two have nothing in common but their place in a step: as a
+// kernel of its own, eight workgroups per object, it took 8 us of every call).
+#define RM_PACK_SPLIT 4
+__device__ inline void pack_weights(const StepArgs& a, int j, int K1) {
+  const int part = j % RM_PACK_SPLIT, op = j / RM_PACK_SPLIT;
+  const int nh = a.mlp_layers, nops = 8 + 2 * (nh - 1);
+  const int so = op / nops, gm = op % nops;
+  const ObjStatic& ob = a.objs[a.sobj[so].obj];
+  const float* W = (a.params_override ? a.params_override : ob.params) + ob.P_grid;
+  const int din = ob.din;
+  const int Ms[8] = {64, 16, 64, 16, 64, 16, 64, K1};
+  const int Ks[8] = {K1, 64, 16, 64, 16, 64, 16, 64};
+  const int offs[8] = {RM_OFF_F1, RM_OFF_F2, RM_OFF_F3, RM_OFF_F4,
+                       RM_OFF_B4, RM_OFF_B3, RM_OFF_B2, RM_OFF_B1};
+  const int64_t stride = RM_WPACK_NH(nh);
+  const int M = gm < 8 ? Ms[gm] : RM_HIDDEN, K = gm < 8 ? Ks[gm] : RM_HIDDEN, Q = K / 16;
+  const int off = gm < 8 ? offs[gm] : RM_OFF_HF(1) + (gm - 8) * RM_HH;
+  float* o32 = a.wpack32 + so * stride + off;
+  uint16_t* o16 = a.wpack16 + so * stride + off;
+  const int per = M * K / RM_PACK_SPLIT;  // M K is a multiple of 1024
+  for (int j = part * per + threadIdx.x; j < (part + 1) * per; j += blockDim.x) {
+    {  // FP32 image
+      const int lane = j & 63, r = (j >> 6) & 3, tq = j >> 8;
+      const int q = tq % Q, t = tq / Q;
+      o32[j] = mlp_A(W, din, nh, gm, 16 * t + (lane & 15), 16 * q + 4 * (lane >> 4) + r);
+    }
+    if (K % 32 == 0) {  // BF16 image of a 16x16x32 operand (slot order of Mma<1>)
+      const int q8 = j & 7, lane = (j >> 3) & 63, tc = j >> 9, C = K / 32;
+      const int c = tc % C, t = tc / C, g = lane >> 4;
+      const int col = 32 * c + (q8 < 4 ? 4 * g + q8 : 16 + 4 * g + (q8 - 4));
+      o16[j] = f2bf(mlp_A(W, din, nh, gm, 16 * t + (lane & 15), col));
+    } else {  // BF16 image of a 16x16x16 operand
+      const int r = j & 3, lane = (j >> 2) & 63, tq = j >> 8;
+      const int q = tq % Q, t = tq / Q;
+      o16[j] = f2bf(mlp_A(W, din, nh, gm, 16 * t + (lane & 15), 16 * q + 4 * (lane >> 4) + r));
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // K1: ray draw, classification, back-projection, box clipping (Sec. V-B)
 template <int NS>
-__global__ __launch_bounds__(256) void k_raygen(StepArgs a) {
+__global__ __launch_bounds__(256) void k_raygen(StepArgs a, int K1) {
+  const int nb = (a.n_rays + 255) / 256;
+  if ((int)blockIdx.x >= nb) return pack_weights(a, blockIdx.x - nb, K1);
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= a.n_rays) return;
   const int si = find_sobj(a.sobj, a.n_sobj, r);
@@ -474,7 +549,9 @@ struct CamArgs {
 };
 
 template <int NS>
-__global__ __launch_bounds__(256) void k_camera_rays(StepArgs a, CamArgs ca) {
+__global__ __launch_bounds__(256) void k_camera_rays(StepArgs a, CamArgs ca, int K1) {
+  const int nb = (a.n_rays + 255) / 256;
+  if ((int)blockIdx.x >= nb) return pack_weights(a, blockIdx.x - nb, K1);
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= a.n_rays) return;
   const int p = ca.pix0 + r;
@@ -491,7 +568,9 @@ __global__ __launch_bounds__(256) void k_camera_rays(StepArgs a, CamArgs ca) {
 
 // caller-given rays (o, d, t_near, t_far) in the object frame
 template <int NS>
-__global__ __launch_bounds__(256) void k_user_rays(StepArgs a, const float* rays) {
+__global__ __launch_bounds__(256) void k_user_rays(StepArgs a, const float* rays, int K1) {
+  const int nb = (a.n_rays + 255) / 256;
+  if ((int)blockIdx.x >= nb) return pack_weights(a, blockIdx.x - nb, K1);
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= a.n_rays) return;
   const float* q = rays + 8 * (int64_t)r;
@@ -623,6 +702,15 @@ __global__ __launch_bounds__(512) void k_encode_fwd(StepArgs a) {
   const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t j = gtid; j < a.n_regions; j += (int64_t)gridDim.x * blockDim.x)
     a.bin_count[j] = 0;  // fresh fill counters for the binned scatter of this pass
+  // Training steps: each object's Adam step advances, after the ray draw, which
+  // uses the step as its counter, and before any Adam update.
+  if (a.fuse_adam && gtid < a.n_sobj) {
+    ObjState* st = a.state + a.sobj[gtid].obj;
+    const int kk = st->step + 1;
+    st->step = kk;
+    st->bc1 = (float)(1.0 - pow((double)a.beta1, (double)kk));
+    st->bc2 = (float)(1.0 - pow((double)a.beta2, (double)kk));
+  }
   // Workgroup i runs on XCD i mod 8; numbered so that each XCD takes a
   // contiguous range of (object, level) blocks, a level's table is gathered
   // by one XCD at a time and stays in its L2: the L2 hit rate goes from 0.67
@@ -682,7 +770,7 @@ __device__ inline void adam1(float& p, float& m, float& v, float g, const StepAr
 }
 
 // Adam on the two features of the table entry at float offset off, with
-// gradient (gx, gy); the object's step has been advanced by the pack kernel.
+// gradient (gx, gy); the object's step has been advanced by the gather kernel.
 __device__ inline void adam_entry(const ObjStatic& ob, int64_t off, float gx, float gy,
                                   const StepArgs& a, float bc1, float bc2) {
   float2 p = *(float2*)(ob.params + off), m = *(float2*)(ob.m + off), v = *(float2*)(ob.v + off);
@@ -1383,85 +1471,6 @@ __global__ __launch_bounds__(RM_FIN_WG) void k_bin_finish(StepArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// K3: MLP weights -> MFMA operand images.  For a GEMM Out(M x 16 samples) =
-// A(M x K) X(K x 16), operand element (t, q, r, lane) is
-// A[16t + lane%16][16q + 4(lane/16) + r]; the FP32 image orders it
-// ((t Q + q) 4 + r) 64 + lane (one 16x16x4 operand per 64 contiguous values),
-// the BF16 image ((t Q + q) 64 + lane) 4 + r (one 16x16x16 operand per lane)
-// when K = 16, and for K a multiple of 32 ((t C + c) 64 + lane) 8 + q8 with
-// A[16t + lane%16][32c + (q8 < 4 ? 4g + q8 : 16 + 4g + q8 - 4)], g = lane/16
-// (one 16x16x32 operand per lane, in the slot order of Mma<1>).
-// Operands 8 + 2(k-1) and 9 + 2(k-1) are the k-th hidden-to-hidden matrix of
-// a deeper density MLP (nh hidden layers) and its transpose.
-__device__ inline float mlp_A(const float* W, int din, int nh, int gemm, int m, int k) {
-  const float* W1 = W;
-  const float* Wh = W1 + RM_HIDDEN * din;
-  const float* W2 = Wh + (nh - 1) * RM_HH;
-  const float* W3 = W2 + RM_DOUT * RM_HIDDEN;
-  const float* W4 = W3 + RM_HIDDEN * RM_GEO;
-  switch (gemm) {
-    case 0: return k < din ? W1[m * din + k] : 0.0f;                 // F1 64 x K1
-    case 1: return W2[m * RM_HIDDEN + k];                             // F2 16 x 64
-    case 2: return k >= 1 ? W3[m * RM_GEO + (k - 1)] : 0.0f;          // F3 64 x 16
-    case 3: return m < 3 ? W4[m * RM_HIDDEN + k] : 0.0f;              // F4 16 x 64
-    case 4: return k < 3 ? W4[k * RM_HIDDEN + m] : 0.0f;              // B4 64 x 16
-    case 5: return m >= 1 ? W3[k * RM_GEO + (m - 1)] : 0.0f;          // B3 16 x 64
-    case 6: return W2[k * RM_HIDDEN + m];                             // B2 64 x 16
-    case 7: return m < din ? W1[k * din + m] : 0.0f;                  // B1 K1 x 64
-    default: {
-      const float* H = Wh + ((gemm - 8) >> 1) * RM_HH;
-      return (gemm & 1) ? H[k * RM_HIDDEN + m] : H[m * RM_HIDDEN + k];  // Wh_k^T, Wh_k
-    }
-  }
-}
-
-// Also advances each object's Adam step (training steps only): after the ray
-// draw, which uses the step as its counter, and before any Adam update.
-__global__ __launch_bounds__(256) void k_pack(StepArgs a, int K1) {
-  const StepObj so = a.sobj[blockIdx.x];
-  const ObjStatic& ob = a.objs[so.obj];
-  if (a.fuse_adam && blockIdx.y == 0 && threadIdx.x == 0) {
-    ObjState* st = a.state + so.obj;
-    const int kk = st->step + 1;
-    st->step = kk;
-    st->bc1 = (float)(1.0 - pow((double)a.beta1, (double)kk));
-    st->bc2 = (float)(1.0 - pow((double)a.beta2, (double)kk));
-  }
-  const float* W = (a.params_override ? a.params_override : ob.params) + ob.P_grid;
-  const int din = ob.din, nh = a.mlp_layers;
-  const int Ms[8] = {64, 16, 64, 16, 64, 16, 64, K1};
-  const int Ks[8] = {K1, 64, 16, 64, 16, 64, 16, 64};
-  const int offs[8] = {RM_OFF_F1, RM_OFF_F2, RM_OFF_F3, RM_OFF_F4,
-                       RM_OFF_B4, RM_OFF_B3, RM_OFF_B2, RM_OFF_B1};
-  const int64_t stride = RM_WPACK_NH(nh);
-  float* o32 = a.wpack32 + (int64_t)blockIdx.x * stride;
-  uint16_t* o16 = a.wpack16 + (int64_t)blockIdx.x * stride;
-  {  // one operand per block
-    const int gm = blockIdx.y;
-    const int M = gm < 8 ? Ms[gm] : RM_HIDDEN, K = gm < 8 ? Ks[gm] : RM_HIDDEN, Q = K / 16;
-    const int off = gm < 8 ? offs[gm] : RM_OFF_HF(1) + (gm - 8) * RM_HH;
-    for (int j = threadIdx.x; j < M * K; j += blockDim.x) {
-      {  // FP32 image
-        const int lane = j & 63, r = (j >> 6) & 3, tq = j >> 8;
-        const int q = tq % Q, t = tq / Q;
-        o32[off + j] = mlp_A(W, din, nh, gm, 16 * t + (lane & 15), 16 * q + 4 * (lane >> 4) + r);
-      }
-      if (K % 32 == 0) {  // BF16 image of a 16x16x32 operand (slot order of Mma<1>)
-        const int q8 = j & 7, lane = (j >> 3) & 63, tc = j >> 9, C = K / 32;
-        const int c = tc % C, t = tc / C, g = lane >> 4;
-        const int col = 32 * c + (q8 < 4 ? 4 * g + q8 : 16 + 4 * g + (q8 - 4));
-        o16[off + j] = f2bf(mlp_A(W, din, nh, gm, 16 * t + (lane & 15), col));
-      } else {  // BF16 image of a 16x16x16 operand
-        const int r = j & 3, lane = (j >> 2) & 63, tq = j >> 8;
-        const int q = tq % Q, t = tq / Q;
-        o16[off + j] =
-            f2bf(mlp_A(W, din, nh, gm, 16 * t + (lane & 15), 16 * q + 4 * (lane >> 4) + r));
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // K4: fused per-ray field kernel.
 //
 // A wave owns one ray at a time; its N samples are processed in blocks of 16.
@@ -1525,7 +1534,7 @@ __device__ inline bf16x4_t cvt_bf16x4(floatx4 v) { return __builtin_convertvecto
 // fragments (features 32c..32c+15 and 32c+16..32c+31) are, concatenated per
 // lane, its B operand: lane (g, n) feeds slots 8g..8g+7 = features
 // 32c + 4g + 0..3 and 32c + 16 + 4g + 0..3 of sample n; the weight image
-// holds A in the same slot order (k_pack).  K = 16 runs as 16x16x16.
+// holds A in the same slot order (pack_weights).  K = 16 runs as 16x16x16.
 template <>
 struct Mma<1> {
   typedef uint16_t wtype;
@@ -2719,9 +2728,16 @@ static inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1
     default: return hipErrorInvalidValue;   \
   }
 
-hipError_t rm_launch_raygen(const StepArgs& a, int NS, hipStream_t st) {
+// Workgroups of a ray kernel: the rays', then the packing's (K1 = 0: none).
+static inline unsigned ray_blocks(const StepArgs& a, int K1) {
+  const unsigned pack = K1 ? a.n_sobj * (8 + 2 * (a.mlp_layers - 1)) * RM_PACK_SPLIT : 0;
+  return cdiv(a.n_rays, 256) + pack;
+}
+
+hipError_t rm_launch_raygen(const StepArgs& a, int NS, int K1, hipStream_t st) {
   if (a.n_rays <= 0) return hipSuccess;
-  RM_NS_SWITCH(NS, (k_raygen<NSC><<<cdiv(a.n_rays, 256), 256, 0, st>>>(a)));
+  if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
+  RM_NS_SWITCH(NS, (k_raygen<NSC><<<ray_blocks(a, K1), 256, 0, st>>>(a, K1)));
   return hipGetLastError();
 }
 
@@ -2754,13 +2770,6 @@ hipError_t rm_launch_bin_acc(const StepArgs& a, const BinGroup& g, hipStream_t s
   StepArgs b = a;
   b.bin_begin = g.bin_begin;
   k_bin_acc<<<g.bin_end - g.bin_begin, RM_ACC_WG, 0, st>>>(b);
-  return hipGetLastError();
-}
-
-hipError_t rm_launch_pack(const StepArgs& a, int K1, hipStream_t st) {
-  if (a.n_sobj <= 0) return hipSuccess;
-  if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
-  k_pack<<<dim3(a.n_sobj, 8 + 2 * (a.mlp_layers - 1)), 256, 0, st>>>(a, K1);
   return hipGetLastError();
 }
 
@@ -2808,8 +2817,9 @@ hipError_t rm_launch_bin_finish(const StepArgs& a, hipStream_t st) {
 
 hipError_t rm_launch_camera_rays(const StepArgs& a, int NS, const float* M, const float* c,
                                  float fx, float fy, float cx, float cy, int W, int pix0,
-                                 hipStream_t st) {
+                                 int K1, hipStream_t st) {
   if (a.n_rays <= 0) return hipSuccess;
+  if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
   CamArgs ca;
   for (int k = 0; k < 9; ++k) ca.M[k] = M[k];
   for (int k = 0; k < 3; ++k) ca.c[k] = c[k];
@@ -2819,13 +2829,15 @@ hipError_t rm_launch_camera_rays(const StepArgs& a, int NS, const float* M, cons
   ca.cy = cy;
   ca.W = W;
   ca.pix0 = pix0;
-  RM_NS_SWITCH(NS, (k_camera_rays<NSC><<<cdiv(a.n_rays, 256), 256, 0, st>>>(a, ca)));
+  RM_NS_SWITCH(NS, (k_camera_rays<NSC><<<ray_blocks(a, K1), 256, 0, st>>>(a, ca, K1)));
   return hipGetLastError();
 }
 
-hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, hipStream_t st) {
+hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, int K1,
+                               hipStream_t st) {
   if (a.n_rays <= 0) return hipSuccess;
-  RM_NS_SWITCH(NS, (k_user_rays<NSC><<<cdiv(a.n_rays, 256), 256, 0, st>>>(a, rays)));
+  if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
+  RM_NS_SWITCH(NS, (k_user_rays<NSC><<<ray_blocks(a, K1), 256, 0, st>>>(a, rays, K1)));
   return hipGetLastError();
 }
 

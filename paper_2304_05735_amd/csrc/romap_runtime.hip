@@ -594,14 +594,12 @@ hipError_t enqueue_step(romap_ctx* c, const Plan& p, const StepArgs& a0, bool ad
 #define RM_MARK(ph) \
   if (prof && (e = mark_phase(c, ph)) != hipSuccess) return e;
   RM_MARK(-1);
-  if ((e = rm_launch_raygen(a, NS, st)) != hipSuccess) return e;
+  if ((e = rm_launch_raygen(a, NS, K1, st)) != hipSuccess) return e;
   RM_MARK(ROMAP_PHASE_RAYGEN);
   if ((e = rm_launch_encode_fwd(a, NS, p.enc_block, st)) != hipSuccess) return e;
   RM_MARK(ROMAP_PHASE_ENCODE);
   if (ev_mid && mid_phase == ROMAP_PHASE_ENCODE && (e = hipEventRecord(ev_mid, st)) != hipSuccess)
     return e;
-  if ((e = rm_launch_pack(a, K1, st)) != hipSuccess) return e;
-  RM_MARK(ROMAP_PHASE_PACK);
   if ((e = rm_launch_field(a, NS, K1, c->cfg.precision, st)) != hipSuccess) return e;
   RM_MARK(ROMAP_PHASE_FIELD);
   if ((e = rm_launch_reduce(a, st)) != hipSuccess) return e;
@@ -740,9 +738,8 @@ romap_status autotune(romap_ctx* c, const std::vector<std::pair<int, int>>& list
     romap_status st = stage_plans(c, {&p});
     if (st != ROMAP_OK) return st;
     StepArgs a = plan_args(c, p);
-    HIPCHK(c, rm_launch_raygen(a, NS, c->stream));
+    HIPCHK(c, rm_launch_raygen(a, NS, K1, c->stream));
     HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
-    HIPCHK(c, rm_launch_pack(a, K1, c->stream));
     StepArgs ar = a;  // the reduce only sums the records here: no loss, no Adam
     ar.mode = RM_MODE_ADJOINT;
     HIPCHK(c, rm_launch_field(a, NS, K1, c->cfg.precision, c->stream));
@@ -1592,9 +1589,8 @@ romap_status romap_render(romap_ctx* c, int32_t id, const romap_camera* cam, flo
     a.out_rgb = d_rgb ? d_rgb + 3 * p0 : nullptr;
     a.out_depth = d_depth ? d_depth + p0 : nullptr;
     a.out_tend = d_tend ? d_tend + p0 : nullptr;
-    HIPCHK(c, rm_launch_camera_rays(a, NS, M, cc, cam->fx, cam->fy, cam->cx, cam->cy, W, (int)p0, c->stream));
+    HIPCHK(c, rm_launch_camera_rays(a, NS, M, cc, cam->fx, cam->fy, cam->cx, cam->cy, W, (int)p0, K1, c->stream));
     HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
-    HIPCHK(c, rm_launch_pack(a, K1, c->stream));
     HIPCHK(c, rm_launch_field(a, NS, K1, c->cfg.precision, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
@@ -2001,7 +1997,7 @@ romap_status romap_debug_rays(romap_ctx* c, int32_t id, int32_t n_rays, int32_t*
   HIPALLOC(c, hipMalloc((void**)&d_kfuv, (size_t)n_rays * 3 * sizeof(int32_t)));
   a.dbg_kfuv = d_kfuv;
   const int NS = c->cfg.samples_per_ray;
-  HIPCHK(c, rm_launch_raygen(a, NS, c->stream));
+  HIPCHK(c, rm_launch_raygen(a, NS, 0, c->stream));
   if (positions) {
     HIPALLOC(c, hipMalloc((void**)&d_pos, (size_t)p.S * 3 * sizeof(float)));
     HIPCHK(c, rm_launch_debug_positions(a, NS, d_pos, c->stream));
@@ -2117,9 +2113,8 @@ static romap_status field_common(romap_ctx* c, int32_t id, const float* params_d
   a = plan_args(c, p);
   a.params_override = params_dev;
   const int NS = c->cfg.samples_per_ray, L = c->cfg.n_levels, K1 = K1_of(c->cfg);
-  HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, c->stream));
+  HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, K1, c->stream));
   HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
-  HIPCHK(c, rm_launch_pack(a, K1, c->stream));
   return ROMAP_OK;
 }
 
@@ -2212,9 +2207,8 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   a.out_rgb = rgb_dev;
   a.out_depth = depth_dev;
   a.out_tend = tend_dev;
-  HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, c->stream));
+  HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, K1, c->stream));
   HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
-  HIPCHK(c, rm_launch_pack(a, K1, c->stream));
   HIPCHK(c, rm_launch_field(a, NS, K1, c->cfg.precision, c->stream));
   // the host copy of the tables must outlive the transfer
   HIPCHK(c, hipStreamSynchronize(c->stream));
