@@ -166,6 +166,10 @@ struct romap_ctx {
   size_t cap_bin_count = 0;
   float* d_rec = nullptr;
   size_t cap_rec = 0;
+  // the plans whose work tables are in d_tables, and what they are of
+  // (stage_cached); empty: unknown
+  std::vector<Plan> staged;
+  std::vector<int64_t> staged_sig;
   // graph of the last batched step
   hipGraphExec_t gexec = nullptr;
   std::vector<int64_t> gsig;
@@ -463,6 +467,7 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // work tables into the table arena.  Plans that run one after another share
 // the scratch buffers; concurrent plans each get their own share of them.
 romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent = false) {
+  c->staged_sig.clear();  // the arena is about to change
   size_t max_rays = 0, max_items = 0, max_sobj = 0, tab = 0, max_rec = 0, max_bins = 0;
   int64_t max_S = 0;
   const size_t L = (size_t)c->cfg.n_levels;
@@ -702,6 +707,46 @@ hipError_t accumulate_phases(romap_ctx* c) {
   return hipSuccess;
 }
 
+// How a call's objects are spread over plans.
+enum PlanKind { kPlanAll = 0, kPlanHalves = 1, kPlanPerObject = 2 };
+
+void split_list(romap_ctx* c, const std::vector<std::pair<int, int>>& list,
+                std::vector<std::pair<int, int>> half[2]);
+
+// The plans of a call, staged: c->staged.  They follow from the objects (their
+// levels never change), the ray counts, the launch shape and the bin cap, so a
+// call of the same as the last finds them in place: no work lists are built,
+// nothing is copied and the host does not wait for the stream (a training loop
+// around the differentiable surface: each call waited for the one before).
+romap_status stage_cached(romap_ctx* c, const std::vector<std::pair<int, int>>& list, PlanKind kind,
+                          int rpi, int blk) {
+  std::vector<int64_t> sig = {kind, rpi, blk, c->debug_bin_cap};
+  for (auto& pr : list) {
+    sig.push_back(pr.first);
+    sig.push_back(pr.second);
+  }
+  if (sig == c->staged_sig) return ROMAP_OK;
+  c->staged_sig.clear();
+  c->staged.clear();
+  if (kind == kPlanPerObject) {
+    c->staged.resize(list.size());
+    for (size_t i = 0; i < list.size(); ++i) build_plan(c, {list[i]}, rpi, blk, c->staged[i]);
+  } else if (kind == kPlanHalves) {
+    std::vector<std::pair<int, int>> hl[2];
+    split_list(c, list, hl);
+    c->staged.resize(2);
+    for (int h = 0; h < 2; ++h) build_plan(c, hl[h], rpi, blk, c->staged[h]);
+  } else {
+    c->staged.resize(1);
+    build_plan(c, list, rpi, blk, c->staged[0]);
+  }
+  std::vector<Plan*> pp;
+  for (Plan& p : c->staged) pp.push_back(&p);
+  const romap_status s = stage_plans(c, pp, kind == kPlanHalves);
+  if (s == ROMAP_OK) c->staged_sig = sig;
+  return s;
+}
+
 std::vector<int64_t> signature(romap_ctx* c, const std::vector<std::pair<int, int>>& list) {
   std::vector<int64_t> s = {c->cfg.samples_per_ray, c->cfg.n_levels, c->cfg.precision};
   for (auto& pr : list) {
@@ -820,14 +865,15 @@ romap_status validate_camera(romap_ctx* c, const romap_camera* cam) {
   return ROMAP_OK;
 }
 
-romap_status read_losses(romap_ctx* c, const Plan& p, std::vector<float>* per_obj, int* n_nan) {
+romap_status read_losses(romap_ctx* c, const std::vector<std::pair<int, int>>& list,
+                         std::vector<float>* per_obj, int* n_nan) {
   std::vector<ObjState> st(c->objs.size());
   HIPCHK(c, hipStreamSynchronize(c->stream));
   HIPCHK(c, hipMemcpy(st.data(), c->d_state, st.size() * sizeof(ObjState), hipMemcpyDeviceToHost));
   per_obj->clear();
   *n_nan = 0;
-  for (auto& so : p.sobj) {
-    const ObjState& s = st[so.obj];
+  for (auto& pr : list) {
+    const ObjState& s = st[pr.first];
     const float l = s.n_loss ? s.loss_acc / (float)s.n_loss : 0.0f;
     if (!std::isfinite(l)) ++*n_nan;
     per_obj->push_back(l);
@@ -1324,6 +1370,7 @@ static std::vector<int64_t> graph_sig(romap_ctx* c, const std::vector<std::pair<
   sig.push_back(blk);
   sig.push_back((int64_t)(uintptr_t)c->d_tables);
   sig.push_back(c->cfg.streams);
+  sig.push_back(c->debug_bin_cap);  // moves the second half's records
   sig.push_back(steps);
   return sig;
 }
@@ -1370,23 +1417,20 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
   for (auto& pr : list) rays_total += pr.second;
   std::vector<float> losses;
   int n_nan = 0;
-  Plan all;
-  build_plan(c, list, rpi, blk, all);
   const bool prof = c->cfg.profile_phases != 0;
   // a batched step of two or more objects runs as two concurrent halves
   const bool split = c->cfg.batch_mode == ROMAP_BATCH_ALL && c->cfg.streams == 2 && !prof &&
                      list.size() >= 2;
-  Plan half[2];
-  if (split) {
-    std::vector<std::pair<int, int>> hl[2];
-    split_list(c, list, hl);
-    build_plan(c, hl[0], rpi, blk, half[0]);
-    build_plan(c, hl[1], rpi, blk, half[1]);
-    if (!c->stream2) {
-      HIPCHK(c, hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking));
-      HIPCHK(c, hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
-      HIPCHK(c, hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
-    }
+  s = stage_cached(c, list, c->cfg.batch_mode != ROMAP_BATCH_ALL ? kPlanPerObject
+                            : split                              ? kPlanHalves
+                                                                 : kPlanAll,
+                   rpi, blk);
+  if (s != ROMAP_OK) return s;
+  const std::vector<Plan>& plans = c->staged;
+  if (split && !c->stream2) {
+    HIPCHK(c, hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking));
+    HIPCHK(c, hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
+    HIPCHK(c, hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
   }
   if (prof) {
     c->pev_n = 0;
@@ -1395,16 +1439,11 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
     c->phase_steps = 0;
   }
   if (c->cfg.batch_mode == ROMAP_BATCH_ALL) {
-    s = split ? stage_plans(c, {&half[0], &half[1]}, true) : stage_plans(c, {&all});
-    if (s != ROMAP_OK) return s;
-    StepArgs a = split ? StepArgs{} : plan_args(c, all);
-    StepArgs ah[2];
-    if (split) {
-      ah[0] = plan_args(c, half[0]);
-      ah[1] = plan_args(c, half[1]);
-    }
+    const Plan& all = plans[0];  // (without a split)
+    const StepArgs a = plan_args(c, all);
+    const StepArgs ah[2] = {a, split ? plan_args(c, plans[1]) : a};
     auto one_step = [&]() -> hipError_t {
-      return split ? enqueue_pair(c, half, ah) : enqueue_step(c, all, a, true);
+      return split ? enqueue_pair(c, plans.data(), ah) : enqueue_step(c, all, a, true);
     };
     if (stats) {
       if (split) {
@@ -1435,7 +1474,7 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
         HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         hipError_t le = hipSuccess;
         if (split)
-          le = enqueue_pair(c, half, ah, G);
+          le = enqueue_pair(c, plans.data(), ah, G);
         else
           for (int k = 0; k < G && le == hipSuccess; ++k) le = enqueue_step(c, all, a, true);
         hipError_t ce = hipStreamEndCapture(c->stream, &graph);
@@ -1457,21 +1496,13 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
     }
     if (stats) {
       HIPCHK(c, hipEventRecord(e1, c->stream));
-      s = read_losses(c, all, &losses, &n_nan);  // per object, in list order
+      s = read_losses(c, list, &losses, &n_nan);  // per object, in list order
       if (s != ROMAP_OK) return s;
     }
   } else {
     // one launch per object per phase (the plain path)
-    std::vector<Plan> plans(list.size());
-    std::vector<Plan*> pp;
-    for (size_t i = 0; i < list.size(); ++i) {
-      build_plan(c, {list[i]}, rpi, blk, plans[i]);
-      pp.push_back(&plans[i]);
-    }
-    s = stage_plans(c, pp);
-    if (s != ROMAP_OK) return s;
     std::vector<StepArgs> args;
-    for (auto& p : plans) args.push_back(plan_args(c, p));
+    for (const Plan& p : plans) args.push_back(plan_args(c, p));
     if (stats) {
       for (auto& a : args) HIPCHK(c, rm_launch_reset_loss(a, c->stream));
       HIPCHK(c, hipEventRecord(e0, c->stream));
@@ -1489,15 +1520,8 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
     }
     if (stats) {
       HIPCHK(c, hipEventRecord(e1, c->stream));
-      losses.clear();
-      for (auto& p : plans) {
-        std::vector<float> l1;
-        int nn = 0;
-        s = read_losses(c, p, &l1, &nn);
-        if (s != ROMAP_OK) return s;
-        losses.insert(losses.end(), l1.begin(), l1.end());
-        n_nan += nn;
-      }
+      s = read_losses(c, list, &losses, &n_nan);
+      if (s != ROMAP_OK) return s;
     }
   }
   if (stats) {
@@ -1529,10 +1553,9 @@ romap_status romap_loss_and_grad(romap_ctx* c, const int32_t* ids, int32_t n, co
     s = autotune(c, list, &rpi, &blk);
     if (s != ROMAP_OK) return s;
   }
-  Plan p;
-  build_plan(c, list, rpi, blk, p);
-  s = stage_plans(c, {&p});
+  s = stage_cached(c, list, kPlanAll, rpi, blk);
   if (s != ROMAP_OK) return s;
+  const Plan& p = c->staged[0];
   for (auto& pr : list) {
     const HostObj& o = c->objs[pr.first];
     HIPCHK(c, rm_launch_fill(o.d_block + o.P_alloc, o.P_alloc, 0.0f, c->stream));
@@ -1543,7 +1566,7 @@ romap_status romap_loss_and_grad(romap_ctx* c, const int32_t* ids, int32_t n, co
   for (auto& pr : list) c->objs[pr.first].grad_dirty = true;
   std::vector<float> l;
   int nn = 0;
-  s = read_losses(c, p, &l, &nn);
+  s = read_losses(c, list, &l, &nn);
   if (s != ROMAP_OK) return s;
   if (losses)
     for (size_t i = 0; i < l.size(); ++i) losses[i] = l[i];
@@ -2101,16 +2124,15 @@ romap_status romap_debug_encode(romap_ctx* c, int32_t id, const float* p, int64_
 }
 
 static romap_status field_common(romap_ctx* c, int32_t id, const float* params_dev,
-                                 const float* rays_dev, int32_t n_rays, Plan& p, StepArgs& a) {
+                                 const float* rays_dev, int32_t n_rays, StepArgs& a) {
   romap_status s = check_object(c, id);
   if (s != ROMAP_OK) return s;
   if (!rays_dev || !ray_count_ok(n_rays, c->cfg.samples_per_ray))
     return fail(c, ROMAP_E_INVALID_ARG, "bad rays");
-  build_plan(c, {{id, n_rays}}, 8, 256, p);
-  p.fins.clear();
-  s = stage_plans(c, {&p});
+  s = stage_cached(c, {{id, n_rays}}, kPlanAll, 8, 256);
   if (s != ROMAP_OK) return s;
-  a = plan_args(c, p);
+  a = plan_args(c, c->staged[0]);
+  a.n_fins = 0;
   a.params_override = params_dev;
   const int NS = c->cfg.samples_per_ray, L = c->cfg.n_levels, K1 = K1_of(c->cfg);
   HIPCHK(c, rm_launch_user_rays(a, NS, rays_dev, K1, c->stream));
@@ -2122,9 +2144,8 @@ romap_status romap_field_forward(romap_ctx* c, int32_t id, const float* params_d
                                  const float* rays_dev, int32_t n_rays, float* rgb_dev,
                                  float* depth_dev, float* tend_dev) {
   if (!c) return ROMAP_E_INVALID_ARG;
-  Plan p;
   StepArgs a;
-  romap_status s = field_common(c, id, params_dev, rays_dev, n_rays, p, a);
+  romap_status s = field_common(c, id, params_dev, rays_dev, n_rays, a);
   if (s != ROMAP_OK) return s;
   a.mode = RM_MODE_FORWARD;
   a.out_rgb = rgb_dev;
@@ -2221,9 +2242,8 @@ romap_status romap_field_backward(romap_ctx* c, int32_t id, const float* params_
                                   float* d_params_dev) {
   if (!c) return ROMAP_E_INVALID_ARG;
   if (!d_params_dev) return fail(c, ROMAP_E_INVALID_ARG, "d_params is NULL");
-  Plan p;
   StepArgs a;
-  romap_status s = field_common(c, id, params_dev, rays_dev, n_rays, p, a);
+  romap_status s = field_common(c, id, params_dev, rays_dev, n_rays, a);
   if (s != ROMAP_OK) return s;
   const HostObj& o = c->objs[id];
   a.mode = RM_MODE_ADJOINT;
@@ -2234,7 +2254,7 @@ romap_status romap_field_backward(romap_ctx* c, int32_t id, const float* params_
   const int NS = c->cfg.samples_per_ray, L = c->cfg.n_levels;
   HIPCHK(c, rm_launch_fill(d_params_dev, o.P, 0.0f, c->stream));
   HIPCHK(c, rm_launch_field(a, NS, K1_of(c->cfg), c->cfg.precision, c->stream));
-  for (const BinGroup& g : p.bgroups) {
+  for (const BinGroup& g : c->staged[0].bgroups) {
     HIPCHK(c, rm_launch_bin_scatter(a, g, NS, c->stream));
     HIPCHK(c, rm_launch_bin_acc(a, g, c->stream));
   }
