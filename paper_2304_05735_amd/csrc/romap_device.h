@@ -148,7 +148,8 @@ struct RayRec {         // 64 B
   float D;              // depth target (ray distance)
   uint32_t flags;
   int32_t obj;
-  int32_t pad0, pad1;
+  int32_t out;          // index of the ray's outputs (forward-only launches)
+  int32_t pad1;
 };
 
 struct StepObj {        // one object of a launch
@@ -241,6 +242,7 @@ struct StepArgs {
   float* out_rgb;
   float* out_depth;
   float* out_tend;
+  int32_t out_opacity;  // out_tend takes 1 - T_end
   int32_t* dbg_kfuv;    // raygen: kf, u, v per ray (may be null)
   int32_t* dbg_cls;
   // binned scatter of the large levels
@@ -248,6 +250,8 @@ struct StepArgs {
   int32_t n_bpairs;
   const BinBlock* bblocks;
   int32_t n_bblocks;
+  int32_t one_nb, one_rpi; // one object (no tables of blocks and items): sample blocks
+                           // per pair, rays per item; else 0
   const Bin* bins;
   int32_t n_bins;
   int32_t bb_begin;     // this launch's first binning block / accumulation workgroup
@@ -269,7 +273,7 @@ hipError_t rm_launch_reduce(const StepArgs& a, hipStream_t st);
 hipError_t rm_launch_bin_finish(const StepArgs& a, hipStream_t st);
 hipError_t rm_launch_camera_rays(const StepArgs& a, int NS, const float* M, const float* c,
                                  float fx, float fy, float cx, float cy, int W, int pix0,
-                                 int K1, hipStream_t st);
+                                 int n_pix, int* n_hit, int K1, hipStream_t st);
 hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, int K1,
                                hipStream_t st);
 // marching cubes over a (res+1)^3 corner grid (x fastest)

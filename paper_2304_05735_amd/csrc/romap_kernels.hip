@@ -531,7 +531,7 @@ __global__ __launch_bounds__(256) void k_raygen(StepArgs a, int K1) {
     }
   }
   R.obj = so.obj;
-  R.pad0 = 0;
+  R.out = r;
   R.pad1 = 0;
   a.rays[r] = R;
   if (a.dbg_kfuv) {
@@ -541,29 +541,49 @@ __global__ __launch_bounds__(256) void k_raygen(StepArgs a, int K1) {
   }
 }
 
-// rays of every pixel of a camera, for rendering (class "object", no target)
+// Rays of n_pix pixels of a camera from pix0 on, for rendering (class "object",
+// no target).
 struct CamArgs {
   float M[9], c[3];
   float fx, fy, cx, cy;
   int W, pix0;
 };
 
+// The pixels whose ray misses the box get their outputs here; the others are
+// appended to the ray records (*n_hit counts them; their order, wave by wave,
+// depends on timing, the outputs do not), so that the gather and the field
+// kernel run over hits alone.
 template <int NS>
-__global__ __launch_bounds__(256) void k_camera_rays(StepArgs a, CamArgs ca, int K1) {
-  const int nb = (a.n_rays + 255) / 256;
+__global__ __launch_bounds__(256) void k_camera_rays(StepArgs a, CamArgs ca, int n_pix, int* n_hit,
+                                                     int K1) {
+  const int nb = (n_pix + 255) / 256;
   if ((int)blockIdx.x >= nb) return pack_weights(a, blockIdx.x - nb, K1);
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= a.n_rays) return;
-  const int p = ca.pix0 + r;
+  const bool in = r < n_pix;
+  const int p = ca.pix0 + (in ? r : n_pix - 1);
   const int obj = a.sobj[0].obj;
   RayRec R;
   pixel_ray(ca.M, ca.c, ca.fx, ca.fy, ca.cx, ca.cy, p % ca.W, p / ca.W, a.objs[obj].half, R, NS);
+  const bool hit = in && (R.flags & RM_F_HIT);
+  if (in && !hit) {
+    if (a.out_rgb) a.out_rgb[3 * (int64_t)p] = a.out_rgb[3 * (int64_t)p + 1] = a.out_rgb[3 * (int64_t)p + 2] = 0.0f;
+    if (a.out_depth) a.out_depth[p] = 0.0f;
+    if (a.out_tend) a.out_tend[p] = a.out_opacity ? 0.0f : 1.0f;
+  }
+  const uint64_t m = __ballot(hit);
+  if (m == 0ull) return;
+  const int lane = threadIdx.x & 63;
+  int first = 0;
+  if (lane == 0) first = atomicAdd(n_hit, __popcll(m));
+  first = __builtin_amdgcn_readfirstlane(first);
+  if (!hit) return;
   R.flags |= RM_CLS_OBJECT;
   R.tgt[0] = R.tgt[1] = R.tgt[2] = 0.0f;
   R.D = 0.0f;
   R.obj = obj;
-  R.pad0 = R.pad1 = 0;
-  a.rays[r] = R;
+  R.out = p;
+  R.pad1 = 0;
+  a.rays[first + __popcll(m & ((1ull << lane) - 1ull))] = R;
 }
 
 // caller-given rays (o, d, t_near, t_far) in the object frame
@@ -588,7 +608,8 @@ __global__ __launch_bounds__(256) void k_user_rays(StepArgs a, const float* rays
   R.tgt[0] = R.tgt[1] = R.tgt[2] = 0.0f;
   R.D = 0.0f;
   R.obj = a.sobj[0].obj;
-  R.pad0 = R.pad1 = 0;
+  R.out = r;
+  R.pad1 = 0;
   a.rays[r] = R;
 }
 
@@ -667,6 +688,22 @@ __device__ inline void gather_hashed(const gptr<const char> G, const Cell& cl, u
   }
 }
 
+// Sample block j of a launch: from the table, or of one object by arithmetic
+// (its pairs all have a.one_nb blocks), so that a call on one object uploads
+// no table that grows with its rays.
+__device__ inline BinBlock block_of(const StepArgs& a, int j) {
+  BinBlock b;
+  if (a.one_nb) {
+    b.pair = j / a.one_nb;
+    b.blk = j - b.pair * a.one_nb;
+  } else {
+    const cptr<BinBlock> q = as_const(a.bblocks + j);
+    b.pair = q->pair;
+    b.blk = q->blk;
+  }
+  return b;
+}
+
 // One level's encoding of the samples at p (unit cube) of a wave's live lanes,
 // added up in slot order; all lanes of the wave call it.
 __device__ inline void encode_wave(const gptr<const char> G, uint32_t N, uint32_t T, bool hashed,
@@ -721,9 +758,9 @@ __global__ __launch_bounds__(512) void k_encode_fwd(StepArgs a) {
   const int per_xcd = (a.n_bblocks + 7) >> 3;
   const int jw = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
   if (jw >= a.n_bblocks) return;
-  const cptr<BinBlock> bb = as_const(a.bblocks + jw);
-  const int blk = bb->blk;
-  const cptr<BinPair> bp = as_const(a.bpairs + bb->pair);
+  const BinBlock bb = block_of(a, jw);
+  const int blk = bb.blk;
+  const cptr<BinPair> bp = as_const(a.bpairs + bb.pair);
   const cptr<ObjStatic> ob = as_const(a.objs + bp->obj);
   const int ray0 = bp->ray_begin + (int)((int64_t)blk * RM_SCAT_WG / NS);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -999,9 +1036,9 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
   const int per_xcd = (a.n_bblocks + 7) >> 3;
   const int jb = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
   if (jb >= a.n_bblocks) return;
-  const cptr<BinBlock> bb = as_const(a.bblocks + a.bb_begin + jb);
-  const int blk = bb->blk;
-  const cptr<BinPair> bp = as_const(a.bpairs + bb->pair);
+  const BinBlock bb = block_of(a, a.bb_begin + jb);
+  const int blk = bb.blk;
+  const cptr<BinPair> bp = as_const(a.bpairs + bb.pair);
   const cptr<ObjStatic> ob = as_const(a.objs + bp->obj);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1754,7 +1791,14 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, n = lane & 15;
-  const Item it = a.items[blockIdx.x];
+  Item it;
+  if (a.one_nb) {  // one object: by arithmetic, as block_of
+    it.so = 0;
+    it.ray_begin = (int)blockIdx.x * a.one_rpi;
+    it.n_rays = a.n_rays - it.ray_begin < a.one_rpi ? a.n_rays - it.ray_begin : a.one_rpi;
+  } else {
+    it = a.items[blockIdx.x];
+  }
   const StepObj so = a.sobj[it.so];
   const ObjStatic& ob = a.objs[so.obj];
   const int L = ob.L, din = ob.din;
@@ -1820,9 +1864,10 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
     const RayRec R = a.rays[ray];
     if (!ray_active(R.flags)) {
       if (FWD && lane == 0) {
-        if (a.out_rgb) a.out_rgb[3 * ray] = a.out_rgb[3 * ray + 1] = a.out_rgb[3 * ray + 2] = 0.0f;
-        if (a.out_depth) a.out_depth[ray] = 0.0f;
-        if (a.out_tend) a.out_tend[ray] = 1.0f;
+        const int64_t o = R.out;
+        if (a.out_rgb) a.out_rgb[3 * o] = a.out_rgb[3 * o + 1] = a.out_rgb[3 * o + 2] = 0.0f;
+        if (a.out_depth) a.out_depth[o] = 0.0f;
+        if (a.out_tend) a.out_tend[o] = a.out_opacity ? 0.0f : 1.0f;
       }
       continue;
     }
@@ -1938,13 +1983,14 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
 
       if constexpr (FWD) {
         if (lane == 0) {
+          const int64_t o = R.out;
           if (a.out_rgb) {
-            a.out_rgb[3 * ray] = Ch[0];
-            a.out_rgb[3 * ray + 1] = Ch[1];
-            a.out_rgb[3 * ray + 2] = Ch[2];
+            a.out_rgb[3 * o] = Ch[0];
+            a.out_rgb[3 * o + 1] = Ch[1];
+            a.out_rgb[3 * o + 2] = Ch[2];
           }
-          if (a.out_depth) a.out_depth[ray] = Dh;
-          if (a.out_tend) a.out_tend[ray] = Tend;
+          if (a.out_depth) a.out_depth[o] = Dh;
+          if (a.out_tend) a.out_tend[o] = a.out_opacity ? 1.0f - Tend : Tend;
         }
         continue;
       } else {
@@ -2729,15 +2775,15 @@ static inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1
   }
 
 // Workgroups of a ray kernel: the rays', then the packing's (K1 = 0: none).
-static inline unsigned ray_blocks(const StepArgs& a, int K1) {
+static inline unsigned ray_blocks(const StepArgs& a, int n, int K1) {
   const unsigned pack = K1 ? a.n_sobj * (8 + 2 * (a.mlp_layers - 1)) * RM_PACK_SPLIT : 0;
-  return cdiv(a.n_rays, 256) + pack;
+  return cdiv(n, 256) + pack;
 }
 
 hipError_t rm_launch_raygen(const StepArgs& a, int NS, int K1, hipStream_t st) {
   if (a.n_rays <= 0) return hipSuccess;
   if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
-  RM_NS_SWITCH(NS, (k_raygen<NSC><<<ray_blocks(a, K1), 256, 0, st>>>(a, K1)));
+  RM_NS_SWITCH(NS, (k_raygen<NSC><<<ray_blocks(a, a.n_rays, K1), 256, 0, st>>>(a, K1)));
   return hipGetLastError();
 }
 
@@ -2817,8 +2863,8 @@ hipError_t rm_launch_bin_finish(const StepArgs& a, hipStream_t st) {
 
 hipError_t rm_launch_camera_rays(const StepArgs& a, int NS, const float* M, const float* c,
                                  float fx, float fy, float cx, float cy, int W, int pix0,
-                                 int K1, hipStream_t st) {
-  if (a.n_rays <= 0) return hipSuccess;
+                                 int n_pix, int* n_hit, int K1, hipStream_t st) {
+  if (n_pix <= 0) return hipSuccess;
   if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
   CamArgs ca;
   for (int k = 0; k < 9; ++k) ca.M[k] = M[k];
@@ -2829,7 +2875,7 @@ hipError_t rm_launch_camera_rays(const StepArgs& a, int NS, const float* M, cons
   ca.cy = cy;
   ca.W = W;
   ca.pix0 = pix0;
-  RM_NS_SWITCH(NS, (k_camera_rays<NSC><<<ray_blocks(a, K1), 256, 0, st>>>(a, ca, K1)));
+  RM_NS_SWITCH(NS, (k_camera_rays<NSC><<<ray_blocks(a, n_pix, K1), 256, 0, st>>>(a, ca, n_pix, n_hit, K1)));
   return hipGetLastError();
 }
 
@@ -2837,7 +2883,7 @@ hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, int
                                hipStream_t st) {
   if (a.n_rays <= 0) return hipSuccess;
   if (a.mlp_layers < 1 || a.mlp_layers > RM_MAX_MLP_LAYERS) return hipErrorInvalidValue;
-  RM_NS_SWITCH(NS, (k_user_rays<NSC><<<ray_blocks(a, K1), 256, 0, st>>>(a, rays, K1)));
+  RM_NS_SWITCH(NS, (k_user_rays<NSC><<<ray_blocks(a, a.n_rays, K1), 256, 0, st>>>(a, rays, K1)));
   return hipGetLastError();
 }
 

@@ -47,6 +47,12 @@ constexpr int64_t kMaxRaysPerCall = int64_t(1) << 30;
 // (22663 camera rays x 128 samples: 885, 808 and 785 us).
 int gather_block(const StepArgs& a) { return a.n_bblocks > 16384 ? 128 : 512; }
 
+// Rays per workgroup of the field kernel in the calls on one object's caller-
+// given rays: 4 (one per wave) until the chip is full of workgroups, 8 beyond
+// (forward and backward of 1999 rays x 128 samples 375 -> 367 us with 4; a
+// forward of 4096 rays x 64 samples 102 -> 106 us).
+int field_rpi(int n_rays, bool forward) { return n_rays <= (forward ? 1024 : 2048) ? 4 : 8; }
+
 bool ray_count_ok(int rays, int samples_per_ray) {
   return rays > 0 && rays <= kMaxRaysPerObject &&
          (int64_t)rays * samples_per_ray <= kMaxSamplesPerObject;
@@ -98,6 +104,9 @@ struct Plan {                 // one launch: its objects, rays and work lists
   int64_t S = 0;
   int rays_per_item = 8;
   int enc_block = 256;
+  int n_items = 0, n_bblocks = 0;
+  int one_nb = 0;            // one object: blocks per pair (items and bblocks stay empty)
+  bool forward = false;      // forward only: no gradient, no records
   size_t off_sobj = 0, off_items = 0, off_fins = 0;  // in the device table arena (bytes)
   size_t off_bpairs = 0, off_bblocks = 0, off_bins = 0;
   // start of the plan's share of each scratch buffer (elements); nonzero for
@@ -166,6 +175,11 @@ struct romap_ctx {
   size_t cap_bin_count = 0;
   float* d_rec = nullptr;
   size_t cap_rec = 0;
+  // rendering: outputs of host calls, hit rays of a pass (device and page-locked host)
+  float* d_image = nullptr;
+  size_t cap_image = 0;
+  int* d_hits = nullptr;
+  int* h_hits = nullptr;
   // the plans whose work tables are in d_tables, and what they are of
   // (stage_cached); empty: unknown
   std::vector<Plan> staged;
@@ -336,26 +350,31 @@ StepArgs base_args(romap_ctx* c) {
   return a;
 }
 
+// Work items of the field kernel; of a single object they are arithmetic and
+// only counted.
 void build_items(Plan& p) {
+  const bool one = p.sobj.size() == 1;
   p.items.clear();
   for (size_t i = 0; i < p.sobj.size(); ++i) {
     StepObj& so = p.sobj[i];
-    so.item_begin = (int)p.items.size();
+    so.item_begin = p.n_items;
     for (int r = 0; r < so.n_rays; r += p.rays_per_item) {
       Item it{};
       it.so = (int)i;
       it.ray_begin = so.ray_begin + r;
       it.n_rays = std::min(p.rays_per_item, so.n_rays - r);
-      p.items.push_back(it);
+      if (!one) p.items.push_back(it);
+      ++p.n_items;
     }
-    so.item_end = (int)p.items.size();
+    so.item_end = p.n_items;
   }
 }
 
 // Builds the work lists of a launch over (object, rays) pairs.
 void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int rays_per_item,
-                int enc_block, Plan& p) {
+                int enc_block, Plan& p, bool forward = false) {
   p = Plan();
+  p.forward = forward;
   p.rays_per_item = rays_per_item;
   p.enc_block = enc_block;
   int ray = 0;
@@ -374,6 +393,12 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
   const int NS = c->cfg.samples_per_ray;
   int64_t grp_rec = 0;  // record memory of the open group (floats)
   std::vector<int> grp_pairs;  // its pairs
+  auto add_blocks = [&](int pair, int nb) {
+    if (p.sobj.size() == 1) p.one_nb = nb;  // the same for each of its pairs
+    else
+      for (int b = 0; b < nb; ++b) p.bblocks.push_back(BinBlock{pair, b});
+    p.n_bblocks += nb;
+  };
   // The accumulation's workgroups go over a group's regions object by object
   // and level by level (in the pairs' order, coarse and fine in turn, one
   // object of 1999 rays x 128 samples took 82 us against 54).
@@ -405,6 +430,8 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       const bool hashed = (o.hashed_mask >> l) & 1u;
       bp.obj = p.sobj[i].obj;
       bp.ray_begin = p.sobj[i].ray_begin;
+      bp.s_begin = (int64_t)p.sobj[i].ray_begin * NS;
+      bp.n_samples = So;
       bp.N = o.N_l[l];
       bp.T = o.T_l[l];
       bp.hashed = hashed;
@@ -431,9 +458,15 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       bp.K = (int)std::max<int64_t>(kmin, std::min<int64_t>(RM_ACC_MAXK,
                                                             (8 * So + bp.R - 1) / bp.R / RM_ACC_CHUNK));
       bp.K = std::max(bp.K, 1);
+      if (forward) {  // the gather's blocks are all that is needed
+        const int pi = (int)p.bpairs.size();
+        p.bpairs.push_back(bp);
+        add_blocks(pi, bp.nb);
+        continue;
+      }
       const int64_t slots = (int64_t)bp.R * bp.cap * (bp.pairs ? 3 : 2);  // floats
       if (p.bgroups.empty() || (grp_rec > 0 && grp_rec + slots > RM_GROUP_FLOATS)) {
-        const int nbb = (int)p.bblocks.size();
+        const int nbb = p.n_bblocks;
         close_group();
         const int nbin = (int)p.bins.size();
         p.bgroups.push_back(BinGroup{nbb, nbb, nbin, nbin});
@@ -444,17 +477,15 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       p.rec_size = std::max(p.rec_size, grp_rec);
       bp.bin_base = (int)p.bin_regions;
       p.bin_regions += bp.R;
-      bp.s_begin = (int64_t)p.sobj[i].ray_begin * NS;
-      bp.n_samples = So;
       const int pi = (int)p.bpairs.size();
       p.bpairs.push_back(bp);
-      for (int b = 0; b < bp.nb; ++b) p.bblocks.push_back(BinBlock{pi, b});
+      add_blocks(pi, bp.nb);
       if (bp.K > 1)
         for (int r = 0; r < bp.R; ++r) {
           const int64_t ne = std::min<int64_t>(RM_RB, (int64_t)o.T_l[l] - (int64_t)r * RM_RB);
           for (int sub = 0; sub * RM_FIN_WG < ne; ++sub) p.fins.push_back(Fin{pi, r, sub, 0});
         }
-      p.bgroups.back().bb_end = (int)p.bblocks.size();
+      p.bgroups.back().bb_end = p.n_bblocks;
       grp_pairs.push_back(pi);
     }
   }
@@ -469,7 +500,7 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent = false) {
   c->staged_sig.clear();  // the arena is about to change
   size_t max_rays = 0, max_items = 0, max_sobj = 0, tab = 0, max_rec = 0, max_bins = 0;
-  int64_t max_S = 0;
+  int64_t max_S = 0, max_de = 0;
   const size_t L = (size_t)c->cfg.n_levels;
   const size_t nh = (size_t)c->cfg.mlp_layers;
   for (Plan* p : plans) {
@@ -481,17 +512,19 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
       p->so_bins = max_bins;
       p->so_rec = max_rec;  // a multiple of 4: the bins' vector loads stay aligned
       max_rays += (size_t)p->n_rays;
-      max_items += p->items.size();
+      max_items += p->forward ? 0 : (size_t)p->n_items;
       max_sobj += p->sobj.size();
       max_S += p->S;
+      max_de = max_S;
       max_rec += (size_t)p->rec_size;
       max_bins += (size_t)p->bin_regions;
     } else {
       p->so_rays = p->so_e = p->so_partials = p->so_wpack = p->so_bins = p->so_rec = 0;
       max_rays = std::max(max_rays, (size_t)p->n_rays);
-      max_items = std::max(max_items, p->items.size());
+      max_items = std::max(max_items, p->forward ? 0 : (size_t)p->n_items);
       max_sobj = std::max(max_sobj, p->sobj.size());
       max_S = std::max(max_S, p->S);
+      if (!p->forward) max_de = std::max(max_de, p->S);
       max_rec = std::max(max_rec, (size_t)p->rec_size);
       max_bins = std::max(max_bins, (size_t)p->bin_regions);
     }
@@ -520,7 +553,7 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
   };
   HIPALLOC(c, regrow(&c->d_rays, &c->cap_rays, std::max<size_t>(max_rays, 1)));
   HIPALLOC(c, regrow(&c->d_e, &c->cap_e, std::max<size_t>(L * (size_t)max_S, 1)));
-  HIPALLOC(c, regrow(&c->d_de, &c->cap_de, std::max<size_t>(L * (size_t)max_S, 1)));
+  HIPALLOC(c, regrow(&c->d_de, &c->cap_de, std::max<size_t>(L * (size_t)max_de, 1)));
   HIPALLOC(c, regrow(&c->d_partials, &c->cap_partials,
                      std::max<size_t>(max_items * RM_REC_STRIDE_NH(nh), 1)));
   HIPALLOC(c, regrow(&c->d_wpack32, &c->cap_w32, std::max<size_t>(max_sobj * RM_WPACK_NH(nh), 1)));
@@ -547,7 +580,9 @@ StepArgs plan_args(romap_ctx* c, const Plan& p) {
   a.sobj = (const StepObj*)(c->d_tables + p.off_sobj);
   a.n_sobj = (int)p.sobj.size();
   a.items = (const Item*)(c->d_tables + p.off_items);
-  a.n_items = (int)p.items.size();
+  a.n_items = p.n_items;
+  a.one_nb = p.one_nb;
+  a.one_rpi = p.rays_per_item;
   a.fins = (const Fin*)(c->d_tables + p.off_fins);
   a.n_fins = (int)p.fins.size();
   a.n_rays = p.n_rays;
@@ -555,7 +590,7 @@ StepArgs plan_args(romap_ctx* c, const Plan& p) {
   a.bpairs = (const BinPair*)(c->d_tables + p.off_bpairs);
   a.n_bpairs = (int)p.bpairs.size();
   a.bblocks = (const BinBlock*)(c->d_tables + p.off_bblocks);
-  a.n_bblocks = (int)p.bblocks.size();
+  a.n_bblocks = p.n_bblocks;
   a.bins = (const Bin*)(c->d_tables + p.off_bins);
   a.n_bins = (int)p.bins.size();
   a.rays = c->d_rays + p.so_rays;
@@ -1041,6 +1076,9 @@ romap_status romap_destroy(romap_ctx* c) {
   hipFree(c->d_mbsum);
   hipFree(c->d_mtris);
   hipFree(c->d_rec);
+  hipFree(c->d_image);
+  hipFree(c->d_hits);
+  if (c->h_hits) hipHostFree(c->h_hits);
   if (c->own_stream) hipStreamDestroy(c->stream);
   delete c;
   return ROMAP_OK;
@@ -1585,53 +1623,65 @@ romap_status romap_render(romap_ctx* c, int32_t id, const romap_camera* cam, flo
   const int64_t npix = (int64_t)W * H;
   float M[9], cc[3];
   object_frame(cam->T_wc, o.box, M, cc);
-  float *d_rgb = nullptr, *d_depth = nullptr, *d_tend = nullptr;
-  if (on_device) {
-    d_rgb = rgb;
-    d_depth = depth;
-  } else {
-    if (rgb) HIPALLOC(c, hipMalloc((void**)&d_rgb, npix * 3 * sizeof(float)));
-    if (depth) HIPALLOC(c, hipMalloc((void**)&d_depth, npix * sizeof(float)));
+  if (npix == 0 || (!rgb && !depth && !opacity)) return ROMAP_OK;
+  // host outputs are rendered into a buffer of the context: rgb, depth, opacity
+  float *d_rgb = rgb, *d_depth = depth, *d_opac = opacity;
+  if (!on_device) {
+    HIPALLOC(c, grow(&c->d_image, &c->cap_image, (size_t)npix * 5));
+    d_rgb = rgb ? c->d_image : nullptr;
+    d_depth = depth ? c->d_image + 3 * npix : nullptr;
+    d_opac = opacity ? c->d_image + 4 * npix : nullptr;
   }
-  if (opacity) HIPALLOC(c, hipMalloc((void**)&d_tend, npix * sizeof(float)));
-  const int chunk = 32768;
-  const int NS = c->cfg.samples_per_ray, L = c->cfg.n_levels, K1 = K1_of(c->cfg);
-  for (int64_t p0 = 0; p0 < npix; p0 += chunk) {
-    const int nr = (int)std::min<int64_t>(chunk, npix - p0);
+  if (!c->d_hits) {
+    HIPALLOC(c, hipMalloc((void**)&c->d_hits, sizeof(int)));
+    HIPALLOC(c, hipHostMalloc((void**)&c->h_hits, sizeof(int), hipHostMallocDefault));
+  }
+  const int NS = c->cfg.samples_per_ray, K1 = K1_of(c->cfg);
+  // pixels per pass (their ray records: 64 MiB) and hit rays per launch (their
+  // encodings: 512 MiB at 16 levels)
+  const int64_t pass = int64_t(1) << 20;
+  const int chunk = (1 << 22) / NS;
+  for (int64_t p0 = 0; p0 < npix; p0 += pass) {
+    const int np = (int)std::min<int64_t>(pass, npix - p0);
+    // one object's tables and packed weights, and room for the pass's rays
     Plan p;
-    build_plan(c, {{id, nr}}, 8, 256, p);
-    p.fins.clear();  // forward only: no Adam, no gradient scatter (the
-    p.bins.clear();  // sample blocks stay: the gather runs over them)
-    p.bgroups.clear();
-    p.rec_size = 0;
-    p.bin_regions = 0;
+    build_plan(c, {{id, 1}}, 8, 256, p, true);
+    p.n_rays = np;  // sizes the ray buffer
     s = stage_plans(c, {&p});
     if (s != ROMAP_OK) return s;
     StepArgs a = plan_args(c, p);
-    a.mode = RM_MODE_FORWARD;
-    a.out_rgb = d_rgb ? d_rgb + 3 * p0 : nullptr;
-    a.out_depth = d_depth ? d_depth + p0 : nullptr;
-    a.out_tend = d_tend ? d_tend + p0 : nullptr;
-    HIPCHK(c, rm_launch_camera_rays(a, NS, M, cc, cam->fx, cam->fy, cam->cx, cam->cy, W, (int)p0, K1, c->stream));
-    HIPCHK(c, rm_launch_encode_fwd(a, NS, gather_block(a), c->stream));
-    HIPCHK(c, rm_launch_field(a, NS, K1, c->cfg.precision, c->stream));
+    a.out_rgb = d_rgb;
+    a.out_depth = d_depth;
+    a.out_tend = d_opac;
+    a.out_opacity = 1;
+    HIPCHK(c, rm_launch_fill((float*)c->d_hits, 1, 0.0f, c->stream));
+    HIPCHK(c, rm_launch_camera_rays(a, NS, M, cc, cam->fx, cam->fy, cam->cx, cam->cy, W, (int)p0, np,
+                                    c->d_hits, K1, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->h_hits, c->d_hits, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    const int hits = *c->h_hits;
+    for (int r0 = 0; r0 < hits; r0 += chunk) {
+      const int nr = std::min(chunk, hits - r0);
+      Plan q;
+      build_plan(c, {{id, nr}}, field_rpi(nr, true), 256, q, true);
+      s = stage_plans(c, {&q});
+      if (s != ROMAP_OK) return s;
+      StepArgs b = plan_args(c, q);
+      b.mode = RM_MODE_FORWARD;
+      b.rays = c->d_rays + r0;
+      b.out_rgb = d_rgb;
+      b.out_depth = d_depth;
+      b.out_tend = d_opac;
+      b.out_opacity = 1;
+      HIPCHK(c, rm_launch_encode_fwd(b, NS, gather_block(b), c->stream));
+      HIPCHK(c, rm_launch_field(b, NS, K1, c->cfg.precision, c->stream));
+    }
   }
   if (!on_device) {
-    if (rgb) HIPCHK(c, hipMemcpy(rgb, d_rgb, npix * 3 * sizeof(float), hipMemcpyDeviceToHost));
-    if (depth) HIPCHK(c, hipMemcpy(depth, d_depth, npix * sizeof(float), hipMemcpyDeviceToHost));
-    hipFree(d_rgb);
-    hipFree(d_depth);
-  }
-  if (opacity) {
-    std::vector<float> t(npix);
-    HIPCHK(c, hipMemcpy(t.data(), d_tend, npix * sizeof(float), hipMemcpyDeviceToHost));
-    for (int64_t i = 0; i < npix; ++i) t[i] = 1.0f - t[i];
-    if (on_device)
-      HIPCHK(c, hipMemcpy(opacity, t.data(), npix * sizeof(float), hipMemcpyHostToDevice));
-    else
-      std::memcpy(opacity, t.data(), npix * sizeof(float));
-    hipFree(d_tend);
+    if (rgb) HIPCHK(c, hipMemcpyAsync(rgb, d_rgb, npix * 3 * sizeof(float), hipMemcpyDeviceToHost, c->stream));
+    if (depth) HIPCHK(c, hipMemcpyAsync(depth, d_depth, npix * sizeof(float), hipMemcpyDeviceToHost, c->stream));
+    if (opacity) HIPCHK(c, hipMemcpyAsync(opacity, d_opac, npix * sizeof(float), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
   }
   return ROMAP_OK;
 }
@@ -2129,7 +2179,7 @@ static romap_status field_common(romap_ctx* c, int32_t id, const float* params_d
   if (s != ROMAP_OK) return s;
   if (!rays_dev || !ray_count_ok(n_rays, c->cfg.samples_per_ray))
     return fail(c, ROMAP_E_INVALID_ARG, "bad rays");
-  s = stage_cached(c, {{id, n_rays}}, kPlanAll, 8, 256);
+  s = stage_cached(c, {{id, n_rays}}, kPlanAll, field_rpi(n_rays, false), 256);
   if (s != ROMAP_OK) return s;
   a = plan_args(c, c->staged[0]);
   a.n_fins = 0;
@@ -2151,6 +2201,8 @@ romap_status romap_field_forward(romap_ctx* c, int32_t id, const float* params_d
   a.out_rgb = rgb_dev;
   a.out_depth = depth_dev;
   a.out_tend = tend_dev;
+  a.one_rpi = field_rpi(n_rays, true);  // nothing but the outputs depends on the items
+  a.n_items = (n_rays + a.one_rpi - 1) / a.one_rpi;
   HIPCHK(c, rm_launch_field(a, c->cfg.samples_per_ray, K1_of(c->cfg), c->cfg.precision, c->stream));
   return ROMAP_OK;
 }
@@ -2166,7 +2218,7 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   if (!c->scratch_dev) return fail(c, ROMAP_E_STATE, "no scratch on this device");
   // the work lists of romap_field_forward (same launch shape, same kernels)
   Plan p;
-  build_plan(c, {{id, n_rays}}, 8, 256, p);
+  build_plan(c, {{id, n_rays}}, field_rpi(n_rays, true), 256, p, true);
   const int NS = c->cfg.samples_per_ray, K1 = K1_of(c->cfg);
   const size_t L = (size_t)c->cfg.n_levels, WP = RM_WPACK_NH(c->cfg.mlp_layers);
   // carve the scratch: tables | bin counters | rays | encodings | packed weights
@@ -2177,9 +2229,7 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
     return here;
   };
   const size_t o_sobj = take(p.sobj.size() * sizeof(StepObj));
-  const size_t o_items = take(p.items.size() * sizeof(Item));
   const size_t o_bpairs = take(p.bpairs.size() * sizeof(BinPair));
-  const size_t o_bblocks = take(p.bblocks.size() * sizeof(BinBlock));
   const size_t tab = at;
   const size_t o_count = take((size_t)p.bin_regions * sizeof(int));
   const size_t o_rays = take((size_t)p.n_rays * sizeof(RayRec));
@@ -2193,24 +2243,23 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   char* base = c->scratch_dev;
   std::vector<char> h(tab);
   std::memcpy(h.data() + o_sobj, p.sobj.data(), p.sobj.size() * sizeof(StepObj));
-  std::memcpy(h.data() + o_items, p.items.data(), p.items.size() * sizeof(Item));
   if (!p.bpairs.empty()) std::memcpy(h.data() + o_bpairs, p.bpairs.data(), p.bpairs.size() * sizeof(BinPair));
-  if (!p.bblocks.empty())
-    std::memcpy(h.data() + o_bblocks, p.bblocks.data(), p.bblocks.size() * sizeof(BinBlock));
   HIPCHK(c, hipMemcpyAsync(base, h.data(), tab, hipMemcpyHostToDevice, c->stream));
   StepArgs a = base_args(c);
   a.sobj = (const StepObj*)(base + o_sobj);
   a.n_sobj = (int)p.sobj.size();
-  a.items = (const Item*)(base + o_items);
-  a.n_items = (int)p.items.size();
+  a.items = nullptr;
+  a.n_items = p.n_items;
+  a.one_nb = p.one_nb;
+  a.one_rpi = p.rays_per_item;
   a.fins = nullptr;
   a.n_fins = 0;
   a.n_rays = p.n_rays;
   a.S = p.S;
   a.bpairs = (const BinPair*)(base + o_bpairs);
   a.n_bpairs = (int)p.bpairs.size();
-  a.bblocks = (const BinBlock*)(base + o_bblocks);
-  a.n_bblocks = (int)p.bblocks.size();
+  a.bblocks = nullptr;
+  a.n_bblocks = p.n_bblocks;
   a.bins = nullptr;
   a.n_bins = 0;
   a.bin_count = (int*)(base + o_count);  // cleared by the gather kernel
