@@ -613,6 +613,36 @@ __global__ __launch_bounds__(256) void k_user_rays(StepArgs a, const float* rays
   a.rays[r] = R;
 }
 
+// Occupancy skip: the live samples of every ray, one bit each (one word per 64
+// samples, the low half of one for 32), tested once here for the gather's 16
+// levels, the field kernel and the binning.  Launched when an object of the
+// launch has occupancy bits.
+template <int NS>
+__global__ __launch_bounds__(256) void k_live(StepArgs a) {
+  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int ray = (int)(s / NS);
+  bool on = false;
+  if (ray < a.n_rays) {
+    const RayRec& R = a.rays[ray];
+    if (ray_active(R.flags)) {
+      const ObjStatic& ob = a.objs[R.obj];
+      on = true;
+      if (ob.occ) {
+        float p[3];
+        sample_pos(R, (int)(s % NS), ob.half, ob.inv2a, p);
+        on = occupied(ob.occ, p);
+      }
+    }
+  }
+  const uint64_t m = __ballot(on);
+  if constexpr (NS >= 64) {
+    if ((threadIdx.x & 63) == 0 && ray < a.n_rays) a.live[s / 64] = m;
+  } else {
+    if ((threadIdx.x & 31) == 0 && ray < a.n_rays)
+      a.live[ray] = (threadIdx.x & 32) ? m >> 32 : m & 0xFFFFFFFFull;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // K2: encoding forward.  One workgroup per block of RM_SCAT_WG samples of one
 // (object, level) pair, blocks ordered object by object and level by level
@@ -685,6 +715,23 @@ __device__ inline void gather_hashed(const gptr<const char> G, const Cell& cl, u
     g[2 * q].y = odd ? sb.y : va[q][1];
     g[2 * q + 1].x = odd ? vb[q][0] : sa.x;
     g[2 * q + 1].y = odd ? vb[q][1] : sa.y;
+  }
+}
+
+// Live samples of the 64 from sample k (a multiple of 64) of ray ray0 on, one
+// bit each (k_live); all ones where nothing is skipped.  Rays past the
+// launch's read the last one's.
+template <int NS>
+__device__ inline uint64_t live_word(const StepArgs& a, int ray0, int k) {
+  if (!a.live) return ~0ull;
+  const int ray = ray0 + k / NS;
+  const cptr<uint64_t> q = as_const(a.live);
+  if constexpr (NS >= 64) {
+    return q[(int64_t)(ray < a.n_rays ? ray : a.n_rays - 1) * (NS / 64) + (k % NS) / 64];
+  } else {
+    const uint64_t lo = q[ray < a.n_rays ? ray : a.n_rays - 1];
+    const uint64_t hi = q[ray + 1 < a.n_rays ? ray + 1 : a.n_rays - 1];
+    return (lo & 0xFFFFFFFFull) | (hi << 32);
   }
 }
 
@@ -769,7 +816,6 @@ __global__ __launch_bounds__(512) void k_encode_fwd(StepArgs a) {
   const uint32_t odd = lane & 1;
   const float* Gp = (a.params_override ? a.params_override : ob->params) + bp->off;
   const gptr<const char> G = as_global((const char*)Gp);
-  const uint32_t* occ = ob->occ;
   const float half[3] = {ob->half[0], ob->half[1], ob->half[2]};
   const float inv[3] = {ob->inv2a[0], ob->inv2a[1], ob->inv2a[2]};
   const uint32_t N = bp->N, T = bp->T;
@@ -783,12 +829,12 @@ __global__ __launch_bounds__(512) void k_encode_fwd(StepArgs a) {
     // the next chunk's ray, in flight during this one
     Rn = wave_ray<NS>(a.rays, a.n_rays, ray0, k + 64 * waves, lane);
     const bool act = k + lane < n && ray_active(R.flags);
-    if (__ballot(act) == 0ull) continue;
+    const bool live = act && ((live_word<NS>(a, ray0, k) >> lane) & 1ull);
+    if (__ballot(live) == 0ull) continue;  // nothing reads a chunk without live samples
     float p[3];
     sample_pos(R, (k + lane) & (NS - 1), half, inv, p);
-    const bool live = act && occupied(occ, p);
-    float ex = 0.0f, ey = 0.0f;  // a skipped sample's encoding is zero
-    if (__ballot(live) != 0ull) encode_wave(G, N, T, hashed, touch, live, p, odd, ex, ey);
+    float ex, ey;  // zero for a skipped sample
+    encode_wave(G, N, T, hashed, touch, live, p, odd, ex, ey);
     if (!act) continue;
     if (a.e_bf16)  // the BF16 MLP reads the encoding rounded to BF16, nothing else
       ((uint32_t*)a.e + at + k)[lane] = pack_bf16x2(ex, ey);
@@ -1045,11 +1091,12 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
   const int R = bp->R, cap = bp->cap;
   for (int r = tid; r < R; r += RM_SCAT_WG) lcnt[r] = 0;
   const int64_t k0 = (int64_t)blk * RM_SCAT_WG;
-  const bool in = k0 + tid < bp->n_samples;
+  const int ray0 = bp->ray_begin + (int)(k0 / NS);
+  const uint64_t lw = live_word<NS>(a, ray0, 64 * wave);
+  const bool in = k0 + tid < bp->n_samples && ((lw >> lane) & 1ull);
   const int64_t at = (int64_t)bp->l * a.S + bp->s_begin + k0;
   const float2 g = in ? (a.de + at)[tid] : make_float2(0.0f, 0.0f);
-  const RayGeo ray = wave_ray<NS>(a.rays, a.n_rays,
-                                  bp->ray_begin + (int)(k0 / NS), 64 * wave, lane);
+  const RayGeo ray = wave_ray<NS>(a.rays, a.n_rays, ray0, 64 * wave, lane);
   const float half[3] = {ob->half[0], ob->half[1], ob->half[2]};
   const float inv[3] = {ob->inv2a[0], ob->inv2a[1], ob->inv2a[2]};
   const uint32_t N = bp->N, T = bp->T;
@@ -1872,6 +1919,14 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
       continue;
     }
     const int64_t sray = (int64_t)ray * NS;
+    // live samples: a block of 16 without any is passed over
+    constexpr int LW = NS > 64 ? NS / 64 : 1;
+    uint64_t lw[LW];
+#pragma unroll
+    for (int j = 0; j < LW; ++j) lw[j] = a.live ? as_const(a.live)[(int64_t)ray * LW + j] : ~0ull;
+    auto block_live = [&](int b) {
+      return ((lw[LW > 1 ? b / 4 : 0] >> (16 * (LW > 1 ? b % 4 : b))) & 0xFFFFull) != 0ull;
+    };
 
     // ---- forward: sigma, colour of every sample ----
     etype EK[NBK][KQ];
@@ -1879,6 +1934,14 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
     for (int b = 0; b < NB; ++b) {
       etype E[KQ];
       floatx4 H1[4], Y[1], H2[4], Z[1];
+      if (!block_live(b)) {
+        if (g == 0) *(floatx4*)(rv + (16 * b + n) * 4) = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (KEEP_E) {
+#pragma unroll
+          for (int q = 0; q < KQ; ++q) EK[KEEP_E ? b : 0][q] = etype{};
+        }
+        continue;
+      }
       load_enc(sray + 16 * b + n, E);
       if (KEEP_E) {
 #pragma unroll
@@ -1939,12 +2002,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
             zc[j][k] = q[1 + k];
             c[j][k] = sigmoidf_(zc[j][k]);
           }
-          bool live = true;
-          if (ob.occ) {
-            float p[3];
-            sample_pos(R, i, ob.half, ob.inv2a, p);
-            live = occupied(ob.occ, p);
-          }
+          const bool live = (lw[LW > 1 ? i / 64 : 0] >> (i & 63)) & 1ull;
           sig[j] = live ? expf(fminf(y0[j], 15.0f)) : 0.0f;
           if (!live) y0[j] = 16.0f;  // no density adjoint either
           tau[j] = sig[j] * R.delta;
@@ -2065,6 +2123,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
       // both their MFMA and their staging
 #pragma unroll(KEEP_E ? NB / 2 : 1)
       for (int bp = 0; bp < NB; bp += 2) {
+        if (!block_live(bp) && !block_live(bp + 1)) continue;
         bf16x4_t E2[2][KQ], H1b[2][4], Yb[2][1], H2b[2][4], dZb[2][1], dH2b[2][4], dYb[2][1],
             dH1b[2][4];
         float dy0[2];
@@ -2169,6 +2228,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
     }
 #pragma unroll(KEEP_E ? NB : 1)
     for (int b = 0; b < NB; ++b) {
+      if (!block_live(b)) continue;
       const int64_t s = sray + 16 * b + n;
       etype E[KQ];
       floatx4 HH[NH][4], Y[1], H2[4];
@@ -2789,6 +2849,7 @@ hipError_t rm_launch_raygen(const StepArgs& a, int NS, int K1, hipStream_t st) {
 
 hipError_t rm_launch_encode_fwd(const StepArgs& a, int NS, int block, hipStream_t st) {
   if (a.n_bblocks <= 0) return hipSuccess;
+  if (a.live) RM_NS_SWITCH(NS, (k_live<NSC><<<cdiv((int64_t)a.n_rays * NS, 256), 256, 0, st>>>(a)));
   // workgroups rounded up to whole rounds of the 8 XCDs
   RM_NS_SWITCH(NS, (k_encode_fwd<NSC><<<8 * ((a.n_bblocks + 7) / 8), block, 0, st>>>(a)));
   return hipGetLastError();

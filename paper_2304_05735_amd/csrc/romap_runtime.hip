@@ -107,6 +107,7 @@ struct Plan {                 // one launch: its objects, rays and work lists
   int n_items = 0, n_bblocks = 0;
   int one_nb = 0;            // one object: blocks per pair (items and bblocks stay empty)
   bool forward = false;      // forward only: no gradient, no records
+  bool skip = false;         // an object has occupancy bits: live masks are made
   size_t off_sobj = 0, off_items = 0, off_fins = 0;  // in the device table arena (bytes)
   size_t off_bpairs = 0, off_bblocks = 0, off_bins = 0;
   // start of the plan's share of each scratch buffer (elements); nonzero for
@@ -161,6 +162,8 @@ struct romap_ctx {
   // scratch of a step
   RayRec* d_rays = nullptr;
   size_t cap_rays = 0;
+  uint64_t* d_live = nullptr;
+  size_t cap_live = 0;
   float2* d_e = nullptr;
   float2* d_de = nullptr;
   size_t cap_e = 0, cap_de = 0;
@@ -375,6 +378,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
                 int enc_block, Plan& p, bool forward = false) {
   p = Plan();
   p.forward = forward;
+  for (auto& pr : list) p.skip = p.skip || c->objs[pr.first].occ_on;
   p.rays_per_item = rays_per_item;
   p.enc_block = enc_block;
   int ray = 0;
@@ -492,6 +496,9 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
   close_group();
 }
 
+// Words of a ray's live mask.
+size_t live_words(romap_ctx* c) { return c->cfg.samples_per_ray > 64 ? c->cfg.samples_per_ray / 64 : 1; }
+
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 // Makes sure the scratch buffers fit a set of plans, then uploads their
@@ -501,6 +508,7 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
   c->staged_sig.clear();  // the arena is about to change
   size_t max_rays = 0, max_items = 0, max_sobj = 0, tab = 0, max_rec = 0, max_bins = 0;
   int64_t max_S = 0, max_de = 0;
+  bool skip = false;
   const size_t L = (size_t)c->cfg.n_levels;
   const size_t nh = (size_t)c->cfg.mlp_layers;
   for (Plan* p : plans) {
@@ -528,6 +536,7 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
       max_rec = std::max(max_rec, (size_t)p->rec_size);
       max_bins = std::max(max_bins, (size_t)p->bin_regions);
     }
+    skip = skip || p->skip;
     p->off_sobj = tab;
     tab += align256(p->sobj.size() * sizeof(StepObj));
     p->off_items = tab;
@@ -552,6 +561,7 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
     return grow(ptr, cap, need);
   };
   HIPALLOC(c, regrow(&c->d_rays, &c->cap_rays, std::max<size_t>(max_rays, 1)));
+  if (skip) HIPALLOC(c, regrow(&c->d_live, &c->cap_live, live_words(c) * std::max<size_t>(max_rays, 1)));
   HIPALLOC(c, regrow(&c->d_e, &c->cap_e, std::max<size_t>(L * (size_t)max_S, 1)));
   HIPALLOC(c, regrow(&c->d_de, &c->cap_de, std::max<size_t>(L * (size_t)max_de, 1)));
   HIPALLOC(c, regrow(&c->d_partials, &c->cap_partials,
@@ -594,6 +604,7 @@ StepArgs plan_args(romap_ctx* c, const Plan& p) {
   a.bins = (const Bin*)(c->d_tables + p.off_bins);
   a.n_bins = (int)p.bins.size();
   a.rays = c->d_rays + p.so_rays;
+  a.live = p.skip ? c->d_live + live_words(c) * p.so_rays : nullptr;
   a.e = c->d_e + p.so_e;
   a.de = c->d_de + p.so_e;
   a.partials = c->d_partials + p.so_partials;
@@ -759,6 +770,7 @@ romap_status stage_cached(romap_ctx* c, const std::vector<std::pair<int, int>>& 
   for (auto& pr : list) {
     sig.push_back(pr.first);
     sig.push_back(pr.second);
+    sig.push_back(c->objs[pr.first].occ_on);
   }
   if (sig == c->staged_sig) return ROMAP_OK;
   c->staged_sig.clear();
@@ -1063,6 +1075,7 @@ romap_status romap_destroy(romap_ctx* c) {
   hipFree(c->d_state);
   hipFree(c->d_kfdev);
   hipFree(c->d_rays);
+  hipFree(c->d_live);
   hipFree(c->d_e);
   hipFree(c->d_de);
   hipFree(c->d_partials);
@@ -1409,6 +1422,7 @@ static std::vector<int64_t> graph_sig(romap_ctx* c, const std::vector<std::pair<
   sig.push_back((int64_t)(uintptr_t)c->d_tables);
   sig.push_back(c->cfg.streams);
   sig.push_back(c->debug_bin_cap);  // moves the second half's records
+  for (auto& pr : list) sig.push_back(c->objs[pr.first].occ_on);  // whether live masks are made
   sig.push_back(steps);
   return sig;
 }
@@ -2233,6 +2247,7 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   const size_t tab = at;
   const size_t o_count = take((size_t)p.bin_regions * sizeof(int));
   const size_t o_rays = take((size_t)p.n_rays * sizeof(RayRec));
+  const size_t o_live = take(p.skip ? (size_t)p.n_rays * live_words(c) * sizeof(uint64_t) : 0);
   const size_t o_e = take(L * (size_t)p.S * sizeof(float2));
   const size_t o_w32 = take(WP * sizeof(float));
   const size_t o_w16 = take(WP * sizeof(uint16_t));
@@ -2266,6 +2281,7 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   a.n_regions = (int)p.bin_regions;
   a.bin_max_R = 0;
   a.rays = (RayRec*)(base + o_rays);
+  a.live = p.skip ? (uint64_t*)(base + o_live) : nullptr;
   a.e = (float2*)(base + o_e);
   a.wpack32 = (float*)(base + o_w32);
   a.wpack16 = (uint16_t*)(base + o_w16);
