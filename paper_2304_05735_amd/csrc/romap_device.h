@@ -50,8 +50,8 @@
 #ifndef RM_MERGE_HASHED
 #define RM_MERGE_HASHED 1
 #endif
-#define RM_PAIR_MAX_RES 2047 /* x-pairs of a level this fine lie in one region of 2^11 entries */
-#define RM_RB_BITS 11       /* binned scatter: table entries per region = 2048 */
+#define RM_RB_BITS 11       /* binned scatter: table entries per region = 2048, */
+#define RM_RB_BITS_MIN 9    /* down to 512 in launches of few regions */
 #define RM_RB (1 << RM_RB_BITS)
 #define RM_ACC_WG 512       /* threads of the region accumulation kernel */
 #ifndef RM_SCAT_WG
@@ -259,6 +259,7 @@ struct StepArgs {
   int32_t bin_begin;
   int32_t n_regions;    // bins over all pairs
   int32_t bin_max_R;    // most regions of one pair
+  int32_t region_bits;  // a region is 2^region_bits table entries (of every pair)
   int32_t* bin_count;   // records per bin (zeroed by the gather kernel)
   float* rec;           // gradient records (corner or pair records, by level)
 };

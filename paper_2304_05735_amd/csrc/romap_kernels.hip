@@ -869,8 +869,8 @@ __device__ inline void adam_entry(const ObjStatic& ob, int64_t off, float gx, fl
 // sample, as a binned scatter.  Float atomics on a table cost per cache line
 // an instruction touches, and on the fine levels no two samples of a ray
 // share a cell, so direct atomics are bound by one line per corner.  Instead
-// the (entry, value) records are sorted into regions of RM_RB entries, and
-// workgroups per region sum them in LDS and update the region of the
+// the (entry, value) records are sorted into regions of 2^region_bits entries,
+// and workgroups per region sum them in LDS and update the region of the
 // gradient with coalesced memory operations:
 //   k_bin_scatter  per block of samples: rank the records per region, reserve
 //                  space in the regions' bins, write them out sorted by region
@@ -1065,7 +1065,7 @@ __device__ inline int block_exclusive_scan(const int* cnt, int2* at, int n, int 
 // Staging: 32 KB, so that four blocks fit a CU: all pair records, and
 // RM_STAGE_CORNERS corner records (a block's further ones, on levels where
 // hardly any merge, are stored straight to their slots).
-template <int NS>
+template <int NS, int RB>
 __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8))) void k_bin_scatter(
     StepArgs a) {
   // dynamic LDS: staging of the sorted records, then two per-region arrays of
@@ -1089,6 +1089,7 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int R = bp->R, cap = bp->cap;
+  constexpr uint32_t em = (1u << RB) - 1u;  // entry within its region
   for (int r = tid; r < R; r += RM_SCAT_WG) lcnt[r] = 0;
   const int64_t k0 = (int64_t)blk * RM_SCAT_WG;
   const int ray0 = bp->ray_begin + (int)(k0 / NS);
@@ -1147,21 +1148,21 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
       const uint32_t diff = (cl.c[0] ^ (cl.c[0] + 1u)) & m;  // 2^kind - 1
       sw = pair_sword(up ? 1.0f - cl.f[0] : cl.f[0], (uint32_t)__popc(diff));
 #pragma unroll
-      for (int q = 0; q < 4; ++q) rank[q] = atomicAdd(&lcnt[idx[q] >> RM_RB_BITS], 1);
+      for (int q = 0; q < 4; ++q) rank[q] = atomicAdd(&lcnt[idx[q] >> RB], 1);
     }
     const int n = place();
     int4* stage = (int4*)dyn;  // slot within the pair's records, then the record
     if (has) {
       int2 b[4];  // all four first: one LDS round trip
 #pragma unroll
-      for (int q = 0; q < 4; ++q) b[q] = rg[idx[q] >> RM_RB_BITS];
+      for (int q = 0; q < 4; ++q) b[q] = rg[idx[q] >> RB];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int slot = b[q].y + rank[q];
-        const PairRec r = pair_pack(av[q].x, av[q].y, sw, idx[q] & (RM_RB - 1));
+        const PairRec r = pair_pack(av[q].x, av[q].y, sw, idx[q] & em);
         const bool fits = slot < cap;
         stage[b[q].x + rank[q]] =
-            make_int4(fits ? (int)(idx[q] >> RM_RB_BITS) * cap + slot : -1, __float_as_int(r.ax),
+            make_int4(fits ? (int)(idx[q] >> RB) * cap + slot : -1, __float_as_int(r.ax),
                       __float_as_int(r.ay), __float_as_int(r.s));
         if (!fits) {  // bin full: direct atomics (correct, only slower)
           const float s = pair_s(r);
@@ -1236,7 +1237,7 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool k0 = (keep >> (2 * q)) & 1u, k1 = (keep >> (2 * q + 1)) & 1u;
-      const uint32_t r0 = idx[2 * q] >> RM_RB_BITS, r1 = idx[2 * q + 1] >> RM_RB_BITS;
+      const uint32_t r0 = idx[2 * q] >> RB, r1 = idx[2 * q + 1] >> RB;
       if (k0 && k1 && r0 == r1) {
         rank[2 * q] = atomicAdd(&lcnt[r0], 2);
         rank[2 * q + 1] = rank[2 * q] + 1;
@@ -1252,13 +1253,13 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
   if (keep) {
     int2 b[8];  // all eight first: one LDS round trip
 #pragma unroll
-    for (int q = 0; q < 8; ++q) b[q] = rg[idx[q] >> RM_RB_BITS];
+    for (int q = 0; q < 8; ++q) b[q] = rg[idx[q] >> RB];
 #pragma unroll
     for (int q = 0; q < 8; ++q)
       if ((keep >> q) & 1u) {
         const int j = b[q].x + rank[q], slot = b[q].y + rank[q];
-        const int at = (int)(idx[q] >> RM_RB_BITS) * cap + slot;
-        const float2 r = rec_pack(v[q], idx[q] & (RM_RB - 1));
+        const int at = (int)(idx[q] >> RB) * cap + slot;
+        const float2 r = rec_pack(v[q], idx[q] & em);
         const bool fits = slot < cap;
         if (j < RM_STAGE_CORNERS) {
           s_val[j] = r;
@@ -1453,9 +1454,10 @@ __global__ __launch_bounds__(RM_ACC_WG) void k_bin_acc(StepArgs a) {
   const bool adam_here = a.fuse_adam && K == 1;
   if (i0 >= i1 && !adam_here) return;  // empty share: nothing to add
   // entries of this region (a dense level's last region is partial)
-  const int64_t e0 = (int64_t)region * RM_RB;
+  const int rsize = 1 << a.region_bits;
+  const int64_t e0 = (int64_t)region * rsize;
   const int64_t rem = (int64_t)bp->T - e0;
-  const int ne = rem < RM_RB ? (int)rem : RM_RB;
+  const int ne = rem < rsize ? (int)rem : rsize;
   const int64_t off0 = bp->off + 2 * e0;  // float offset of the region
   // Adam operands of this thread's entries, loaded now so that they arrive
   // while the records are summed
@@ -1475,7 +1477,7 @@ __global__ __launch_bounds__(RM_ACC_WG) void k_bin_acc(StepArgs a) {
       }
     }
   }
-  for (int e = threadIdx.x; e < RM_RB; e += RM_ACC_WG) {
+  for (int e = threadIdx.x; e < rsize; e += RM_ACC_WG) {
     emax[e] = 0u;
     acc[e] = 0ull;
     acc[RM_RB + e] = 0ull;
@@ -1542,9 +1544,10 @@ __global__ __launch_bounds__(RM_FIN_WG) void k_bin_finish(StepArgs a) {
   const BinPair bp = a.bpairs[f.pair];
   const int oi = a.sobj[bp.so].obj;
   const ObjStatic& ob = a.objs[oi];
-  const int64_t e0 = (int64_t)f.region * RM_RB;
+  const int rsize = 1 << a.region_bits;
+  const int64_t e0 = (int64_t)f.region * rsize;
   const int64_t rem = (int64_t)ob.T_l[bp.l] - e0;
-  const int ne = rem < RM_RB ? (int)rem : RM_RB;
+  const int ne = rem < rsize ? (int)rem : rsize;
   const int e = f.sub * RM_FIN_WG + threadIdx.x;
   if (e >= ne) return;
   const int64_t off = ob.off[bp.l] + 2 * (e0 + e);
@@ -2855,20 +2858,33 @@ hipError_t rm_launch_encode_fwd(const StepArgs& a, int NS, int block, hipStream_
   return hipGetLastError();
 }
 
+// The region size is a constant of the instance: as a value read at run time,
+// the binning of 24 objects x 2048 rays took 419 us instead of 387.
+#define RM_RB_SWITCH(RB, CALL)                        \
+  switch (RB) {                                       \
+    case 9: { constexpr int RBC = 9; CALL; break; }   \
+    case 10: { constexpr int RBC = 10; CALL; break; } \
+    case 11: { constexpr int RBC = 11; CALL; break; } \
+    default: return hipErrorInvalidValue;             \
+  }
+
 hipError_t rm_launch_bin_scatter(const StepArgs& a, const BinGroup& g, int NS, hipStream_t st) {
   if (g.bb_end <= g.bb_begin) return hipSuccess;
   const size_t lds = RM_STAGE_BYTES + (size_t)a.bin_max_R * (sizeof(int2) + sizeof(int));
   if (lds > 65536) {  // beyond the default dynamic LDS limit (tables of 2^22+ entries)
     hipError_t e0 = hipSuccess;
-    RM_NS_SWITCH(NS, (e0 = hipFuncSetAttribute((const void*)k_bin_scatter<NSC>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds)));
+    RM_RB_SWITCH(a.region_bits,
+                 RM_NS_SWITCH(NS, (e0 = hipFuncSetAttribute((const void*)k_bin_scatter<NSC, RBC>,
+                                                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                            (int)lds))));
     if (e0 != hipSuccess) return e0;
   }
   StepArgs b = a;
   b.bb_begin = g.bb_begin;
   b.n_bblocks = g.bb_end - g.bb_begin;  // the group's blocks
-  RM_NS_SWITCH(NS, (k_bin_scatter<NSC><<<8 * ((b.n_bblocks + 7) / 8), RM_SCAT_WG, lds, st>>>(b)));
+  const dim3 grid(8 * ((b.n_bblocks + 7) / 8));
+  RM_RB_SWITCH(a.region_bits,
+               RM_NS_SWITCH(NS, (k_bin_scatter<NSC, RBC><<<grid, RM_SCAT_WG, lds, st>>>(b))));
   return hipGetLastError();
 }
 

@@ -107,6 +107,7 @@ struct Plan {                 // one launch: its objects, rays and work lists
   int n_items = 0, n_bblocks = 0;
   int one_nb = 0;            // one object: blocks per pair (items and bblocks stay empty)
   bool forward = false;      // forward only: no gradient, no records
+  int region_bits = RM_RB_BITS;  // a region is 2^region_bits table entries
   bool skip = false;         // an object has occupancy bits: live masks are made
   size_t off_sobj = 0, off_items = 0, off_fins = 0;  // in the device table arena (bytes)
   size_t off_bpairs = 0, off_bblocks = 0, off_bins = 0;
@@ -393,6 +394,18 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
   p.n_rays = ray;
   p.S = (int64_t)ray * c->cfg.samples_per_ray;
   build_items(p);
+  // Regions of 2^11 entries, halved while they are fewer than the CUs: a region
+  // is summed by one workgroup, and a small model has few of them (8 levels of
+  // 2^12 entries: 16 regions of 2^11, 21.5 us; 64 of 2^9, 8.5). Not smaller for
+  // more: x-pairs of corners must stay in a region.
+  auto regions = [](uint32_t T, int rb) { return (int)((T + (1u << rb) - 1u) >> rb); };
+  int& rb = p.region_bits;
+  for (rb = RM_RB_BITS; rb > RM_RB_BITS_MIN; --rb) {
+    int64_t n = 0;
+    for (auto& so : p.sobj)
+      for (int l = 0; l < c->objs[so.obj].L; ++l) n += regions(c->objs[so.obj].T_l[l], rb);
+    if (n >= 256) break;
+  }
   // binned gradient scatter: every (object, level) pair
   const int NS = c->cfg.samples_per_ray;
   int64_t grp_rec = 0;  // record memory of the open group (floats)
@@ -429,7 +442,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       bp.so = (int)i;
       bp.l = l;
       bp.nb = (int)((So + RM_SCAT_WG - 1) / RM_SCAT_WG);
-      bp.R = (int)((o.T_l[l] + RM_RB - 1) >> RM_RB_BITS);
+      bp.R = regions(o.T_l[l], rb);
       bp.touch = (int)o.N_l[l] <= 4 * NS;
       const bool hashed = (o.hashed_mask >> l) & 1u;
       bp.obj = p.sobj[i].obj;
@@ -442,10 +455,10 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       bp.off = o.off[l];
       // Corners shared by consecutive samples of a ray are merged on coarse
       // levels; on finer hashed ones x-pairs of corners are the records, half
-      // as many at 3/4 of the bytes (a level as fine as a whole region keeps
-      // corner records: a pair may straddle two regions).
+      // as many at 3/4 of the bytes (a level with as many cells a side as a
+      // region has entries keeps corner records: a pair may straddle regions).
       bp.merge = (int)o.N_l[l] <= (hashed ? RM_MERGE_HASHED : RM_MERGE_DENSE) * NS;
-      bp.pairs = hashed && !bp.merge && (int)o.N_l[l] <= RM_PAIR_MAX_RES;
+      bp.pairs = hashed && !bp.merge && o.N_l[l] < (1u << rb);
       // records per region: per_sample So / R on average (uniform hash, z-slabs
       // of a dense level); hashed: near-uniform counts, the mean plus 8
       // standard deviations; dense: twice the mean (a full bin falls back to
@@ -486,7 +499,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       add_blocks(pi, bp.nb);
       if (bp.K > 1)
         for (int r = 0; r < bp.R; ++r) {
-          const int64_t ne = std::min<int64_t>(RM_RB, (int64_t)o.T_l[l] - (int64_t)r * RM_RB);
+          const int64_t ne = std::min<int64_t>(1 << rb, (int64_t)o.T_l[l] - ((int64_t)r << rb));
           for (int sub = 0; sub * RM_FIN_WG < ne; ++sub) p.fins.push_back(Fin{pi, r, sub, 0});
         }
       p.bgroups.back().bb_end = p.n_bblocks;
@@ -615,6 +628,7 @@ StepArgs plan_args(romap_ctx* c, const Plan& p) {
   a.n_regions = (int)p.bin_regions;
   a.bin_max_R = 0;
   for (const BinPair& bp : p.bpairs) a.bin_max_R = std::max(a.bin_max_R, bp.R);
+  a.region_bits = p.region_bits;
   return a;
 }
 
