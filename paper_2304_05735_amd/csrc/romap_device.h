@@ -23,11 +23,13 @@
 #define RM_WG 256           /* threads of the fused field kernel (4 waves) */
 #define RM_FIN_WG 512       /* entries per workgroup of the finishing kernel */
 // Threads of the MLP reduction: small workgroups start beside the other
-// object group's kernels as soon as one of theirs finishes (with 1024 the
-// kernel took 86-144 us there against 11 us alone; with 256, 34-43 us; step
-// 1.710 -> 1.702 ms on 24 objects, 512: 1.703).
+// object group's kernels as soon as one of theirs finishes (24 objects: 22 us
+// there with 256 threads, 32 with 512, 114 with 1024, against 14 alone).
 #ifndef RM_RED_WG
 #define RM_RED_WG 256
+#endif
+#ifndef RM_RED_COLS
+#define RM_RED_COLS 32 /* record columns of a reduction block */
 #endif
 #define RM_GRAPH_MIN_STEPS 8 /* steps of a romap_train call that repay a graph capture */
 #ifndef RM_GRAPH_STEPS

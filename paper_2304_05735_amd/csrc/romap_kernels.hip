@@ -2391,30 +2391,37 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
 // ---------------------------------------------------------------------------
 // K5: per-object MLP gradient and loss from the work-item records, summed in
 // a fixed order (deterministic); in a training step the MLP's Adam update is
-// applied here, else the gradient is written.  A block owns
-// 256 record columns, 4 per lane (column RM_REC_LOSS_NH is the loss); its 16
-// waves sum interleaved sixteenths of the items, then combine in LDS.
+// applied here, else the gradient is written.  A block owns 32 record columns
+// (column RM_REC_LOSS_NH is the loss), read 4 per lane: eight lanes take a
+// 128-byte line of an item's record, and the 32 such runs of lanes sum
+// interleaved 32nds of the items, then combine in LDS.  Bound by the records'
+// read; with 256 columns to a block, one object's launch was 17 blocks of four
+// waves, too few for it (512 items: 24 us, now 5; beside the other half's
+// kernels 6 objects 48 -> 23, 24 objects 35 -> 22; 64 columns: 27 and 21, and
+// 16: 24 and 24).
 __global__ __launch_bounds__(RM_RED_WG) void k_reduce(StepArgs a) {
-  constexpr int NW = RM_RED_WG / 64;
-  __shared__ float4 s_part[NW][64];
+  constexpr int LPI = RM_RED_COLS / 4, NQ = RM_RED_WG / LPI;
+  constexpr int PW = 64 / LPI;  // runs side by side in a wave
+  static_assert(PW >= 4, "one lane per column at the end");
+  __shared__ float4 s_part[NQ][LPI];
   const StepObj so = a.sobj[blockIdx.y];
   const ObjStatic& ob = a.objs[so.obj];
   const int nm = (int)(ob.P - ob.P_grid);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j0 = blockIdx.x * 256 + 4 * lane;  // 4 columns per lane (the stride is a multiple of 4)
+  const int col = threadIdx.x % LPI, part = threadIdx.x / LPI;
+  const int j0 = blockIdx.x * RM_RED_COLS + 4 * col;  // 4 columns per lane (the stride is a multiple of 4)
   float4 s[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) s[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   const int stride = RM_REC_STRIDE_NH(a.mlp_layers), rloss = RM_REC_LOSS_NH(a.mlp_layers);
   if (j0 < stride) {
-    // wave w sums items w, w + NW, ...: four per lane in flight, each into
-    // its own partial sum (a fixed order: deterministic)
-    const float* col = a.partials + j0;
-    for (int it = so.item_begin + wave; it < so.item_end; it += 4 * NW) {
+    // run w of lanes sums items w, w + NQ, ...: four per lane in flight, each
+    // into its own partial sum (a fixed order: deterministic)
+    const float* rec = a.partials + j0;
+    for (int it = so.item_begin + part; it < so.item_end; it += 4 * NQ) {
       float4 x[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        x[u] = it + u * NW < so.item_end ? *(const float4*)(col + (int64_t)(it + u * NW) * stride)
+        x[u] = it + u * NQ < so.item_end ? *(const float4*)(rec + (int64_t)(it + u * NQ) * stride)
                                          : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -2422,39 +2429,42 @@ __global__ __launch_bounds__(RM_RED_WG) void k_reduce(StepArgs a) {
       }
     }
   }
-  s_part[wave][lane] = make_float4((s[0].x + s[1].x) + (s[2].x + s[3].x),
-                                   (s[0].y + s[1].y) + (s[2].y + s[3].y),
-                                   (s[0].z + s[1].z) + (s[2].z + s[3].z),
-                                   (s[0].w + s[1].w) + (s[2].w + s[3].w));
+  s_part[part][col] = make_float4((s[0].x + s[1].x) + (s[2].x + s[3].x),
+                                  (s[0].y + s[1].y) + (s[2].y + s[3].y),
+                                  (s[0].z + s[1].z) + (s[2].z + s[3].z),
+                                  (s[0].w + s[1].w) + (s[2].w + s[3].w));
   __syncthreads();
-  if (wave != 0 || j0 >= stride) return;
-  float4 t = s_part[0][lane];
+  if (threadIdx.x >= 64) return;
+  float4 t = s_part[part][col];
 #pragma unroll
-  for (int w = 1; w < NW; ++w) {  // fixed order: deterministic
-    const float4 u = s_part[w][lane];
+  for (int w = 1; w < NQ / PW; ++w) {  // fixed order: deterministic
+    const float4 u = s_part[PW * w + part][col];
     t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
   }
-  const float tv[4] = {t.x, t.y, t.z, t.w};
-  float* gdst = a.grad_override ? a.grad_override : ob.grad;
-  const float bc1 = a.state[so.obj].bc1, bc2 = a.state[so.obj].bc2;
+  // the runs together, then lane (part, col) takes column 4 col + part
+  float tv[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const int j = j0 + c;
-    if (j < nm) {
-      const int64_t o = ob.P_grid + j;
-      if (a.fuse_adam) {  // training step: the MLP gradient is complete here
-        adam1(ob.params[o], ob.m[o], ob.v[o], tv[c], a, bc1, bc2);
-      } else {
-        gdst[o] = tv[c];
-      }
-    } else if (j == rloss && a.mode == RM_MODE_TRAIN) {
-      ObjState* st = a.state + so.obj;
-      st->loss_acc += tv[c];
-      st->n_loss += 1;
+#pragma unroll
+    for (int m = LPI; m < 64; m *= 2) tv[c] += __shfl_xor(tv[c], m);
+  }
+  if (part >= 4) return;
+  const float g = part == 0 ? tv[0] : part == 1 ? tv[1] : part == 2 ? tv[2] : tv[3];
+  const int j = j0 + part;
+  float* gdst = a.grad_override ? a.grad_override : ob.grad;
+  if (j < nm) {
+    const int64_t o = ob.P_grid + j;
+    if (a.fuse_adam) {  // training step: the MLP gradient is complete here
+      adam1(ob.params[o], ob.m[o], ob.v[o], g, a, a.state[so.obj].bc1, a.state[so.obj].bc2);
+    } else {
+      gdst[o] = g;
     }
+  } else if (j == rloss && a.mode == RM_MODE_TRAIN) {
+    ObjState* st = a.state + so.obj;
+    st->loss_acc += g;
+    st->n_loss += 1;
   }
 }
-
 
 // ---------------------------------------------------------------------------
 // Density of an object's field at normalised positions in [0,1]^3: encoding
@@ -2927,7 +2937,7 @@ hipError_t rm_launch_field(const StepArgs& a, int NS, int K1, int prec, hipStrea
 
 hipError_t rm_launch_reduce(const StepArgs& a, hipStream_t st) {
   if (a.n_sobj <= 0) return hipSuccess;
-  dim3 grid(cdiv(RM_REC_LOSS_NH(a.mlp_layers) + 1, 256), a.n_sobj);
+  dim3 grid(cdiv(RM_REC_LOSS_NH(a.mlp_layers) + 1, RM_RED_COLS), a.n_sobj);
   k_reduce<<<grid, RM_RED_WG, 0, st>>>(a);
   return hipGetLastError();
 }
