@@ -224,6 +224,7 @@ struct StepArgs {
   RayRec* rays;
   int32_t n_rays;
   uint64_t* live;       // live samples of each ray, or null (no object skips any)
+  int32_t live_step;    // words from one ray's to the next's
   float2* e;            // [L][S] encodings (e_bf16: [L][S] uint32, a BF16 pair each)
   int e_bf16;           // encodings stored rounded to BF16 (the BF16 MLP reads nothing else)
   float2* de;           // [L][S] their adjoints

@@ -636,10 +636,11 @@ __global__ __launch_bounds__(256) void k_live(StepArgs a) {
   }
   const uint64_t m = __ballot(on);
   if constexpr (NS >= 64) {
-    if ((threadIdx.x & 63) == 0 && ray < a.n_rays) a.live[s / 64] = m;
+    if ((threadIdx.x & 63) == 0 && ray < a.n_rays)
+      a.live[(int64_t)ray * a.live_step + (s % NS) / 64] = m;
   } else {
     if ((threadIdx.x & 31) == 0 && ray < a.n_rays)
-      a.live[ray] = (threadIdx.x & 32) ? m >> 32 : m & 0xFFFFFFFFull;
+      a.live[(int64_t)ray * a.live_step] = (threadIdx.x & 32) ? m >> 32 : m & 0xFFFFFFFFull;
   }
 }
 
@@ -727,10 +728,10 @@ __device__ inline uint64_t live_word(const StepArgs& a, int ray0, int k) {
   const int ray = ray0 + k / NS;
   const cptr<uint64_t> q = as_const(a.live);
   if constexpr (NS >= 64) {
-    return q[(int64_t)(ray < a.n_rays ? ray : a.n_rays - 1) * (NS / 64) + (k % NS) / 64];
+    return q[(int64_t)(ray < a.n_rays ? ray : a.n_rays - 1) * a.live_step + (k % NS) / 64];
   } else {
-    const uint64_t lo = q[ray < a.n_rays ? ray : a.n_rays - 1];
-    const uint64_t hi = q[ray + 1 < a.n_rays ? ray + 1 : a.n_rays - 1];
+    const uint64_t lo = q[(int64_t)(ray < a.n_rays ? ray : a.n_rays - 1) * a.live_step];
+    const uint64_t hi = q[(int64_t)(ray + 1 < a.n_rays ? ray + 1 : a.n_rays - 1) * a.live_step];
     return (lo & 0xFFFFFFFFull) | (hi << 32);
   }
 }
@@ -1926,7 +1927,7 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
     constexpr int LW = NS > 64 ? NS / 64 : 1;
     uint64_t lw[LW];
 #pragma unroll
-    for (int j = 0; j < LW; ++j) lw[j] = a.live ? as_const(a.live)[(int64_t)ray * LW + j] : ~0ull;
+    for (int j = 0; j < LW; ++j) lw[j] = a.live ? as_const(a.live)[(int64_t)ray * a.live_step + j] : ~0ull;
     auto block_live = [&](int b) {
       return ((lw[LW > 1 ? b / 4 : 0] >> (16 * (LW > 1 ? b % 4 : b))) & 0xFFFFull) != 0ull;
     };

@@ -618,6 +618,7 @@ StepArgs plan_args(romap_ctx* c, const Plan& p) {
   a.n_bins = (int)p.bins.size();
   a.rays = c->d_rays + p.so_rays;
   a.live = p.skip ? c->d_live + live_words(c) * p.so_rays : nullptr;
+  a.live_step = (int)live_words(c);
   a.e = c->d_e + p.so_e;
   a.de = c->d_de + p.so_e;
   a.partials = c->d_partials + p.so_partials;
@@ -2261,7 +2262,6 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   const size_t tab = at;
   const size_t o_count = take((size_t)p.bin_regions * sizeof(int));
   const size_t o_rays = take((size_t)p.n_rays * sizeof(RayRec));
-  const size_t o_live = take(p.skip ? (size_t)p.n_rays * live_words(c) * sizeof(uint64_t) : 0);
   const size_t o_e = take(L * (size_t)p.S * sizeof(float2));
   const size_t o_w32 = take(WP * sizeof(float));
   const size_t o_w16 = take(WP * sizeof(uint16_t));
@@ -2295,7 +2295,13 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
   a.n_regions = (int)p.bin_regions;
   a.bin_max_R = 0;
   a.rays = (RayRec*)(base + o_rays);
-  a.live = p.skip ? (uint64_t*)(base + o_live) : nullptr;
+  // the live masks in the ray records' targets, which a forward has no use
+  // for: they take no scratch of their own
+  static_assert(offsetof(RayRec, tgt) % 8 == 0 && offsetof(RayRec, D) == offsetof(RayRec, tgt) + 12 &&
+                    sizeof(RayRec) % 8 == 0,
+                "two words of 64 bits at tgt");
+  a.live = p.skip ? (uint64_t*)a.rays[0].tgt : nullptr;
+  a.live_step = sizeof(RayRec) / sizeof(uint64_t);
   a.e = (float2*)(base + o_e);
   a.wpack32 = (float*)(base + o_w32);
   a.wpack16 = (uint16_t*)(base + o_w16);

@@ -100,3 +100,33 @@ def test_dead_blocks_forward(N, prec):
                 ref[k] = w
             else:
                 assert np.array_equal(ref[k], w), k
+
+
+@pytest.mark.parametrize("N,L", [(32, 1), (64, 2), (128, 1)])
+def test_noalloc_scratch_with_skips(N, L):
+    """The most rays whose records, encodings and work tables (16 bytes per 8
+    rays, 8 per level and 512 samples) fill the 64 MiB of scratch: skipped
+    samples must not need room of their own."""
+    print(f"noalloc scratch N {N} L {L}", flush=True)
+    frames, box = tiny_scene()
+    g, _, gid = make_pair(L, 16, 64, 12, N, 64, frames, box)
+    p = random_params(g.object_info(gid).n_grid_params, 2 * L, seed=N).astype(np.float32)
+    g.set_params(gid, p)
+    g.set_occupancy(gid, _slab_bits(80, 110))
+    n = int(((64 << 20) - (96 << 10)) / (64 + 2 + L * N / 64 + 8 * L * N))
+    rng = np.random.default_rng(N)
+    o = rng.normal(size=(n, 3))
+    o = 1.5 * o / np.linalg.norm(o, axis=1, keepdims=True)
+    d = rng.uniform(-1, 1, (n, 3)) * np.asarray(box["half"]) - o
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    rays = torch.from_numpy(np.concatenate([o, d, np.full((n, 1), 0.9), np.full((n, 1), 2.1)],
+                                           1).astype(np.float32)).cuda()
+    torch.cuda.synchronize()
+    out = g.field_forward(gid, rays)
+    g.sync()
+    same = [torch.full_like(x, float("nan")) for x in out]
+    torch.cuda.synchronize()
+    g.field_forward_noalloc(gid, rays, *same)
+    g.sync()
+    for a, b in zip(out, same):
+        assert torch.equal(a, b)
