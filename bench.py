@@ -492,7 +492,7 @@ def trace_summary(d, workload, steps, warmup, frames=300):
     else:
         run = f"--workload {workload} --steps {steps} --warmup {warmup} --only-headline --streams 1"
         what = (f"# {steps + warmup} steps ({warmup} warm-up + {steps} timed) replay the step graph "
-                "on one stream; extra calls of k_field / k_encode_fwd / k_pack / k_raygen come "
+                "on one stream; extra calls of k_field / k_encode_fwd / k_raygen come "
                 "from the autotuner and the graph capture; k_field<PREC, NS, K1, layers>")
     out = [f"# rocprofv3 kernel-trace summary: training-step kernels, workload {workload} "
            f"({WORKLOAD_NOTES.get(workload, workload)})",
