@@ -1863,11 +1863,25 @@ __global__ __launch_bounds__(RM_WG) __attribute__((
   const int mode = a.mode;
 
   {  // weights of this object into LDS (16-byte copies)
-    const uint4* src = (const uint4*)((PREC ? (const void*)(a.wpack16 + (int64_t)it.so * WP)
-                                            : (const void*)(a.wpack32 + (int64_t)it.so * WP)));
-    uint4* dst = (uint4*)s_w;
+    const floatx4* src = (const floatx4*)((PREC ? (const void*)(a.wpack16 + (int64_t)it.so * WP)
+                                                : (const void*)(a.wpack32 + (int64_t)it.so * WP)));
+    floatx4* dst = (floatx4*)s_w;
     constexpr int NV = WBYTES / 16;
-    for (int j = tid; j < NV; j += RM_WG) dst[j] = src[j];
+    // up to ten loads in flight, then their stores: one round trip to the L2
+    // (64 items of 4 rays: kernel 19.8 -> 18.6 us; 24 objects 178 -> 175)
+    constexpr int DEEP = NV / RM_WG < 10 ? (NV + RM_WG - 1) / RM_WG : 10;
+#pragma unroll
+    for (int j0 = 0; j0 < NV; j0 += DEEP * RM_WG) {
+      floatx4 t[DEEP];
+#pragma unroll
+      for (int u = 0; u < DEEP; ++u) {
+        const int j = j0 + u * RM_WG + tid;
+        t[u] = src[j < NV ? j : NV - 1];
+      }
+#pragma unroll
+      for (int u = 0; u < DEEP; ++u)
+        if (j0 + u * RM_WG + tid < NV) dst[j0 + u * RM_WG + tid] = t[u];
+    }
   }
   __syncthreads();
 
