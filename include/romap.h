@@ -28,6 +28,11 @@
  *    current HIP device; work on them is ordered on the context's stream and
  *    is complete once that stream has synchronised.
  *  - One thread at a time per context; several contexts may coexist.
+ *  - Calls whose kernels use the context's (or the library's) scratch memory
+ *    -- romap_train, romap_loss_and_grad, romap_render, romap_debug_rays and the
+ *    romap_field_* calls -- return ROMAP_E_STATE, and do nothing, while the
+ *    context's stream is being captured into a graph: a replay would run on
+ *    scratch that later calls overwrite or free.
  *  - Cameras are pinhole, x right, y down, z forward, pixel centres at +0.5;
  *    T_wc is the row-major 3x4 camera-to-world pose.  World +z is up; an
  *    object's yaw turns about +z (roll = pitch = 0, Sec. IV-B).
@@ -348,8 +353,8 @@ romap_status romap_field_backward(romap_ctx* ctx, int32_t object_id, const float
                                   const float* d_depth_dev, const float* d_tend_dev,
                                   float* d_params_dev);
 
-/* For callers that cannot allocate device memory (code being captured into
- * a graph, tight serving loops, harnesses that forbid allocation): the same
+/* For callers that cannot allocate device memory (tight serving loops,
+ * harnesses that forbid allocation): the same
  * result as romap_field_forward (same kernels and launch shape, bit for bit)
  * with no allocation of any kind on the device.  Its rays, encodings, packed
  * weights and work tables live in one 64 MiB array of the library on each

@@ -909,6 +909,18 @@ hipError_t scratch_address(char** out) {
   return hipSuccess;
 }
 
+// Calls whose kernels read or write the context's scratch do not join a stream
+// capture: a replay would run on work tables and buffers that any later call
+// may overwrite or free.  (Staging waits for the stream, which a capture
+// refuses by itself; a call that finds its tables in place does not stage.)
+romap_status check_not_capturing(romap_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  HIPCHK(c, hipStreamIsCapturing(c->stream, &st));
+  if (st != hipStreamCaptureStatusNone)
+    return fail(c, ROMAP_E_STATE, "the context's stream is being captured: this call uses the context's scratch");
+  return ROMAP_OK;
+}
+
 romap_status check_object(romap_ctx* c, int32_t id) {
   if (id < 0 || id >= (int32_t)c->objs.size())
     return fail(c, ROMAP_E_NOT_FOUND, "unknown object id " + std::to_string(id));
@@ -1461,6 +1473,8 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
   if (s != ROMAP_OK) return s;
   if (stats) std::memset(stats, 0, sizeof(*stats));
   if (list.empty() || n_steps == 0) return ROMAP_OK;
+  s = check_not_capturing(c);
+  if (s != ROMAP_OK) return s;
   int rpi = c->fixed_rpi, blk = c->fixed_blk;
   if (c->cfg.autotune) {
     s = autotune(c, list, &rpi, &blk);
@@ -1615,6 +1629,8 @@ romap_status romap_loss_and_grad(romap_ctx* c, const int32_t* ids, int32_t n, co
   romap_status s = resolve_list(c, ids, n, rays, list);
   if (s != ROMAP_OK) return s;
   if (list.empty()) return ROMAP_OK;
+  s = check_not_capturing(c);
+  if (s != ROMAP_OK) return s;
   int rpi = c->fixed_rpi, blk = c->fixed_blk;  // the launch shape of a training step
   if (c->cfg.autotune) {
     s = autotune(c, list, &rpi, &blk);
@@ -1653,6 +1669,8 @@ romap_status romap_render(romap_ctx* c, int32_t id, const romap_camera* cam, flo
   float M[9], cc[3];
   object_frame(cam->T_wc, o.box, M, cc);
   if (npix == 0 || (!rgb && !depth && !opacity)) return ROMAP_OK;
+  s = check_not_capturing(c);
+  if (s != ROMAP_OK) return s;
   // host outputs are rendered into a buffer of the context: rgb, depth, opacity
   float *d_rgb = rgb, *d_depth = depth, *d_opac = opacity;
   if (!on_device) {
@@ -2089,6 +2107,8 @@ romap_status romap_debug_rays(romap_ctx* c, int32_t id, int32_t n_rays, int32_t*
   if (s != ROMAP_OK) return s;
   if (n_rays <= 0 || n_rays > (1 << 22)) return fail(c, ROMAP_E_INVALID_ARG, "bad ray count");
   if (c->objs[id].kfs.empty()) return fail(c, ROMAP_E_STATE, "object has no keyframe");
+  s = check_not_capturing(c);
+  if (s != ROMAP_OK) return s;
   Plan p;
   build_plan(c, {{id, n_rays}}, 8, 256, p);
   s = stage_plans(c, {&p});
@@ -2208,6 +2228,8 @@ static romap_status field_common(romap_ctx* c, int32_t id, const float* params_d
   if (s != ROMAP_OK) return s;
   if (!rays_dev || !ray_count_ok(n_rays, c->cfg.samples_per_ray))
     return fail(c, ROMAP_E_INVALID_ARG, "bad rays");
+  s = check_not_capturing(c);
+  if (s != ROMAP_OK) return s;
   s = stage_cached(c, {{id, n_rays}}, kPlanAll, field_rpi(n_rays, false), 256);
   if (s != ROMAP_OK) return s;
   a = plan_args(c, c->staged[0]);
@@ -2269,6 +2291,8 @@ romap_status romap_field_forward_noalloc(romap_ctx* c, int32_t id, const float* 
     return fail(c, ROMAP_E_INVALID_ARG,
                 "noalloc forward needs " + std::to_string(at) + " bytes of scratch, more than its " +
                     std::to_string(RM_SCRATCH_BYTES) + " (fewer rays per call)");
+  s = check_not_capturing(c);
+  if (s != ROMAP_OK) return s;
   char* base = c->scratch_dev;
   std::vector<char> h(tab);
   std::memcpy(h.data() + o_sobj, p.sobj.data(), p.sobj.size() * sizeof(StepObj));
