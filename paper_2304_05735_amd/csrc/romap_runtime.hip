@@ -33,8 +33,9 @@ std::string g_create_error;
 // Ray-count limits.  One object's step writes at most 8 gradient records per
 // sample and level, all of them possibly into one region of a small dense
 // level: rays x samples <= 2^27 keeps that count, the region's bin counter
-// and its capacity within int32.  Ray indices of a step are int32: at most
-// 2^30 rays over the objects of one call.
+// and its capacity within int32.  The slots of all regions of a level are
+// kept within int32 by the capacity (build_plan).  Ray indices of a step are
+// int32: at most 2^30 rays over the objects of one call.
 constexpr int kMaxRaysPerObject = 1 << 22;
 constexpr int64_t kMaxSamplesPerObject = int64_t(1) << 27;
 constexpr int64_t kMaxRaysPerCall = int64_t(1) << 30;
@@ -468,6 +469,7 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
       const int64_t want = hashed ? expect + 8 * (int64_t)std::ceil(std::sqrt((double)expect)) + 256
                                   : 2 * expect + 1024;
       bp.cap = (int)((std::min<int64_t>(want, all) + 3) & ~(int64_t)3);
+      bp.cap = std::min(bp.cap, (INT32_MAX / bp.R) & ~3);  // slots of a level: int32
       if (c->debug_bin_cap > 0) bp.cap = std::min(bp.cap, (c->debug_bin_cap + 3) & ~3);
       // workgroups per region: about RM_ACC_CHUNK corners each, and at most
       // 2^(62 - RM_FX_BITS) / 2 records per workgroup so no fixed-point sum can overflow

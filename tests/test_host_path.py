@@ -92,3 +92,17 @@ for k, call in enumerate(calls):
     fake.fake_capture(0)
     assert code(call) == 0 and fake.fake_launches() > n, k
 """)
+
+
+@pytest.mark.parametrize("base,log2T", [(252, 24), (160, 24), (16, 19)])
+def test_record_slots_fit_their_index(fake, base, log2T):
+    """A record's slot within its level is a 32-bit number, also for the most
+    samples that one object takes (2^27: 8 records each, and a dense level's
+    bins twice that)."""
+    fake(f"""
+g, (i,), cam = context(n_levels=1, base_res={base}, max_res=1024, log2_table_size={log2T},
+                       samples_per_ray=128)
+backward(g, i, 1 << 20)
+print(fake.fake_max_record_slots())
+assert (1 << 30) <= fake.fake_max_record_slots() < (1 << 31)
+""")
