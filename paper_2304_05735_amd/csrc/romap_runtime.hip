@@ -511,6 +511,16 @@ void build_plan(romap_ctx* c, const std::vector<std::pair<int, int>>& list, int 
   close_group();
 }
 
+// Lets go of the captured step graph once its last launch has run: calls
+// without stats do not wait for their steps.
+void drop_graph(romap_ctx* c) {
+  if (!c->gexec) return;
+  hipStreamSynchronize(c->stream);
+  hipGraphExecDestroy(c->gexec);
+  c->gexec = nullptr;
+  c->gsig.clear();
+}
+
 // Words of a ray's live mask.
 size_t live_words(romap_ctx* c) { return c->cfg.samples_per_ray > 64 ? c->cfg.samples_per_ray / 64 : 1; }
 
@@ -567,12 +577,7 @@ romap_status stage_plans(romap_ctx* c, std::vector<Plan*> plans, bool concurrent
   }
   auto regrow = [&](auto** ptr, size_t* cap, size_t need) -> hipError_t {
     if (need <= *cap) return hipSuccess;
-    // a reallocation invalidates the captured graph
-    if (c->gexec) {
-      hipGraphExecDestroy(c->gexec);
-      c->gexec = nullptr;
-      c->gsig.clear();
-    }
+    drop_graph(c);  // a reallocation invalidates the captured graph
     return grow(ptr, cap, need);
   };
   HIPALLOC(c, regrow(&c->d_rays, &c->cap_rays, std::max<size_t>(max_rays, 1)));
@@ -1082,7 +1087,7 @@ romap_status romap_create(const romap_config* cfg, void* hip_stream, romap_ctx**
 romap_status romap_destroy(romap_ctx* c) {
   if (!c) return ROMAP_E_INVALID_ARG;
   hipStreamSynchronize(c->stream);
-  if (c->gexec) hipGraphExecDestroy(c->gexec);
+  drop_graph(c);
   if (c->stream2) {
     hipStreamSynchronize(c->stream2);
     hipStreamDestroy(c->stream2);
@@ -1189,11 +1194,7 @@ romap_status romap_add_object(romap_ctx* c, int32_t instance_id, const romap_box
       c->d_objs = nd;
       c->d_state = ns;
       c->cap_objs = c->cap_state = ncap;
-      if (c->gexec) {
-        hipGraphExecDestroy(c->gexec);
-        c->gexec = nullptr;
-        c->gsig.clear();
-      }
+      drop_graph(c);
     }
   }
   HIPALLOC(c, hipMalloc((void**)&o.d_block, 4 * (size_t)o.P_alloc * sizeof(float)));
@@ -1382,11 +1383,7 @@ romap_status romap_add_keyframe(romap_ctx* c, const romap_camera* cam, const uin
       hipFree(c->d_kfdev);
       c->d_kfdev = nd;
       c->cap_kfdev = ncap;
-      if (c->gexec) {
-        hipGraphExecDestroy(c->gexec);
-        c->gexec = nullptr;
-        c->gsig.clear();
-      }
+      drop_graph(c);
     } else if (nd) {
       hipFree(nd);
     }
@@ -1549,10 +1546,7 @@ romap_status romap_train(romap_ctx* c, const int32_t* ids, int32_t n, int32_t n_
       const int G = graph_steps(n_steps);
       std::vector<int64_t> sig = graph_sig(c, list, rpi, blk, G);
       if (!c->gexec || sig != c->gsig) {
-        if (c->gexec) {
-          hipGraphExecDestroy(c->gexec);
-          c->gexec = nullptr;
-        }
+        drop_graph(c);
         hipGraph_t graph;
         HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         hipError_t le = hipSuccess;

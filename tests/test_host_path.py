@@ -106,3 +106,26 @@ backward(g, i, 1 << 20)
 print(fake.fake_max_record_slots())
 assert (1 << 30) <= fake.fake_max_record_slots() < (1 << 31)
 """)
+
+
+def test_step_graph_is_destroyed_after_its_last_launch(fake):
+    """Calls without stats do not wait, so the graph that another step count,
+    another set of rays or a buffer's growth replaces may still run."""
+    fake("""
+g, ids, cam = context(n=2, use_graph=2)
+g.train(8, ids, stats=False)
+assert fake.fake_graph_launches() == 2
+g.train(2, ids, stats=False)               # a graph of one step takes its place
+g.train(8, ids, [40, 30], stats=False)
+backward(g, ids[0], 5000)                  # buffers grow
+g.train(8, ids, stats=False)
+for k in range(2, 18):
+    g.add_object(k + 1, [0, 0, 0], 0.0, [0.4] * 3)   # the object table grows
+g.train(8, ids, stats=False)
+for k in range(70):
+    g.add_keyframe(cam, np.zeros((2, 4, 3), np.uint8), np.zeros((2, 4), np.int32))
+g.train(8, ids, stats=False)
+assert fake.fake_graph_launches() == 2 + 2 + 2 + 2 + 2 + 2
+g.close()
+assert fake.fake_busy_graphs_destroyed() == 0, fake.fake_busy_graphs_destroyed()
+""")
