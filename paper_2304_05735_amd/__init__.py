@@ -196,11 +196,21 @@ def mc_case(m: int):
 
 
 class Context:
-    """Owns one romap_ctx.  Methods map one-to-one onto the C ABI."""
+    """Owns one romap_ctx.  Methods map one-to-one onto the C ABI.
+
+    ``stream``: the torch stream that orders the context's work.  torch's
+    default stream has no handle of its own (a NULL handle asks the library for
+    a stream of the context), so a context made with it works on a side stream
+    that the calls on device tensors order with torch's current stream.
+    ``None``: a stream of the context, ordered by ``sync`` alone.
+    """
 
     def __init__(self, cfg: romap_config | None = None, stream=None, **kw):
         self.cfg = cfg if cfg is not None else default_config(**kw)
         h = C.c_void_p()
+        self._side = None
+        if stream is not None and stream.cuda_stream == 0:
+            stream = self._side = torch.cuda.Stream(stream.device)
         st = None if stream is None else C.c_void_p(stream.cuda_stream)
         self._check(lib().romap_create(C.byref(self.cfg), st, C.byref(h)), None)
         self.h = h
@@ -209,6 +219,16 @@ class Context:
         if rc != ROMAP_OK:
             hh = self.h if h == "self" else None
             raise RomapError(rc, lib().romap_last_error(hh).decode())
+
+    def _after_torch(self):
+        """The context's work from here on follows what torch has queued."""
+        if self._side is not None and not torch.cuda.is_current_stream_capturing():
+            self._side.wait_stream(torch.cuda.current_stream(self._side.device))
+
+    def _before_torch(self):
+        """What torch queues from here on follows the context's work."""
+        if self._side is not None and not torch.cuda.is_current_stream_capturing():
+            torch.cuda.current_stream(self._side.device).wait_stream(self._side)
 
     def close(self):
         if getattr(self, "h", None):
@@ -293,6 +313,7 @@ class Context:
         n = C.c_int64(0)
         if isinstance(grid, torch.Tensor):
             g = grid.contiguous().float()
+            self._after_torch()
             self._check(lib().romap_marching_cubes(self.h, _ptr(g), int(res), float(iso), _ptr(lo),
                                                    _ptr(hi), None, 0, C.byref(n), 1))
             out = torch.empty((max(n.value, 1), 3, 3), dtype=torch.float32, device=g.device)
@@ -322,8 +343,10 @@ class Context:
     def query_density(self, oid, xyz):
         if isinstance(xyz, torch.Tensor):
             sig = torch.empty(xyz.shape[0], dtype=torch.float32, device=xyz.device)
+            self._after_torch()
             self._check(lib().romap_query_density(self.h, int(oid), _ptr(xyz), xyz.shape[0],
                                                   _ptr(sig), 1))
+            self._before_torch()
             return sig
         xyz = np.ascontiguousarray(xyz, np.float32).reshape(-1, 3)
         sig = np.zeros(xyz.shape[0], np.float32)
@@ -377,8 +400,10 @@ class Context:
         rgb = torch.empty(n, 3, device=dev)
         depth = torch.empty(n, device=dev)
         tend = torch.empty(n, device=dev)
+        self._after_torch()
         self._check(lib().romap_field_forward(self.h, int(oid), _ptr(params), _ptr(rays), n,
                                               _ptr(rgb), _ptr(depth), _ptr(tend)))
+        self._before_torch()
         return rgb, depth, tend
 
     def field_forward_noalloc(self, oid, rays, rgb, depth, tend, params=None):
@@ -390,6 +415,7 @@ class Context:
                     or tuple(t.shape) != shape or not t.is_contiguous()):
                 raise ValueError(f"field_forward_noalloc: expected a contiguous float32 device "
                                  f"tensor of shape {shape}")
+        self._after_torch()
         self._check(lib().romap_field_forward_noalloc(self.h, int(oid), _ptr(params), _ptr(rays),
                                                       rays.shape[0], _ptr(rgb), _ptr(depth),
                                                       _ptr(tend)))
@@ -398,9 +424,11 @@ class Context:
         n = rays.shape[0]
         P = self.n_params(oid)
         out = torch.empty(P, device=rays.device)
+        self._after_torch()
         self._check(lib().romap_field_backward(self.h, int(oid), _ptr(params), _ptr(rays), n,
                                                _ptr(d_rgb), _ptr(d_depth), _ptr(d_tend),
                                                _ptr(out)))
+        self._before_torch()
         return out
 
     def set_occupancy(self, oid, bits):
