@@ -27,6 +27,7 @@
 // out where wanted), so positions and indices are reproducible bit for bit.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <math.h>
 #include <stdint.h>
@@ -619,28 +620,31 @@ __global__ __launch_bounds__(256) void k_user_rays(StepArgs a, const float* rays
 // launch has occupancy bits.
 template <int NS>
 __global__ __launch_bounds__(256) void k_live(StepArgs a) {
-  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int ray = (int)(s / NS);
-  bool on = false;
-  if (ray < a.n_rays) {
-    const RayRec& R = a.rays[ray];
-    if (ray_active(R.flags)) {
-      const ObjStatic& ob = a.objs[R.obj];
-      on = true;
-      if (ob.occ) {
-        float p[3];
-        sample_pos(R, (int)(s % NS), ob.half, ob.inv2a, p);
-        on = occupied(ob.occ, p);
+  const int lane = threadIdx.x & 63;
+  const int64_t n = (int64_t)a.n_rays * NS, stride = (int64_t)gridDim.x * 256;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + (threadIdx.x - lane); k < n; k += stride) {
+    const int64_t s = k + lane;
+    const int ray = (int)(s / NS);
+    bool on = false;
+    if (ray < a.n_rays) {
+      const RayRec& R = a.rays[ray];
+      if (ray_active(R.flags)) {
+        const ObjStatic& ob = a.objs[R.obj];
+        on = true;
+        if (ob.occ) {
+          float p[3];
+          sample_pos(R, (int)(s % NS), ob.half, ob.inv2a, p);
+          on = occupied(ob.occ, p);
+        }
       }
     }
-  }
-  const uint64_t m = __ballot(on);
-  if constexpr (NS >= 64) {
-    if ((threadIdx.x & 63) == 0 && ray < a.n_rays)
-      a.live[(int64_t)ray * a.live_step + (s % NS) / 64] = m;
-  } else {
-    if ((threadIdx.x & 31) == 0 && ray < a.n_rays)
-      a.live[(int64_t)ray * a.live_step] = (threadIdx.x & 32) ? m >> 32 : m & 0xFFFFFFFFull;
+    const uint64_t m = __ballot(on);
+    if constexpr (NS >= 64) {
+      if (lane == 0) a.live[(int64_t)ray * a.live_step + (s % NS) / 64] = m;
+    } else {
+      if ((lane & 31) == 0 && ray < a.n_rays)
+        a.live[(int64_t)ray * a.live_step] = (lane & 32) ? m >> 32 : m & 0xFFFFFFFFull;
+    }
   }
 }
 
@@ -2870,6 +2874,10 @@ __global__ void k_fill(float* x, int64_t n, float v) {
 
 static inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
+// A launch takes fewer than 2^32 work-items: kernels that may have more run
+// over their work in rounds, or in several launches, of this many.
+constexpr int64_t kMaxWorkItems = int64_t(1) << 28;
+
 #define RM_NS_SWITCH(NS, CALL)              \
   switch (NS) {                             \
     case 32: { constexpr int NSC = 32; CALL; break; }   \
@@ -2893,7 +2901,8 @@ hipError_t rm_launch_raygen(const StepArgs& a, int NS, int K1, hipStream_t st) {
 
 hipError_t rm_launch_encode_fwd(const StepArgs& a, int NS, int block, hipStream_t st) {
   if (a.n_bblocks <= 0) return hipSuccess;
-  if (a.live) RM_NS_SWITCH(NS, (k_live<NSC><<<cdiv((int64_t)a.n_rays * NS, 256), 256, 0, st>>>(a)));
+  const int64_t live = std::min((int64_t)a.n_rays * NS, kMaxWorkItems);
+  if (a.live) RM_NS_SWITCH(NS, (k_live<NSC><<<cdiv(live, 256), 256, 0, st>>>(a)));
   // workgroups rounded up to whole rounds of the 8 XCDs
   RM_NS_SWITCH(NS, (k_encode_fwd<NSC><<<8 * ((a.n_bblocks + 7) / 8), block, 0, st>>>(a)));
   return hipGetLastError();
@@ -3007,11 +3016,16 @@ hipError_t rm_launch_user_rays(const StepArgs& a, int NS, const float* rays, int
 
 hipError_t rm_launch_query_density(const ObjStatic* objs, int obj, int nh, const float* xyz,
                                    int64_t n, float* sigma, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const unsigned nb = cdiv(n, 64);
-  if (nh > 1) k_query_density<true><<<nb, RM_DENS_WG, 0, st>>>(objs, obj, xyz, n, sigma);
-  else k_query_density<false><<<nb, RM_DENS_WG, 0, st>>>(objs, obj, xyz, n, sigma);
-  return hipGetLastError();
+  constexpr int64_t per = kMaxWorkItems / (RM_DENS_WG / 64);  // points of a launch
+  for (; n > 0; n -= per, xyz += 3 * per, sigma += per) {
+    const int64_t m = std::min(n, per);
+    const unsigned nb = cdiv(m, 64);
+    if (nh > 1) k_query_density<true><<<nb, RM_DENS_WG, 0, st>>>(objs, obj, xyz, m, sigma);
+    else k_query_density<false><<<nb, RM_DENS_WG, 0, st>>>(objs, obj, xyz, m, sigma);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t rm_launch_density_grid(const ObjStatic* objs, int obj, int nh, int res, float* grid,

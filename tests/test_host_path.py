@@ -129,3 +129,19 @@ assert fake.fake_graph_launches() == 2 + 2 + 2 + 2 + 2 + 2
 g.close()
 assert fake.fake_busy_graphs_destroyed() == 0, fake.fake_busy_graphs_destroyed()
 """)
+
+
+def test_launches_stay_below_the_grid_limit(fake):
+    """The runtime takes fewer than 2^32 work-items to a launch: densities at
+    2^32 - 64 points, and live masks of 2^32 samples."""
+    fake("""
+g, (i,), cam = context()
+n = (1 << 32) - 64
+g._check(L.romap_query_density(g.h, i, here, n, here, 1))
+assert fake.fake_threads(b"k_query_density") >= 4 * n
+g, ids, cam = context(n=32, n_levels=1, samples_per_ray=128, streams=1, use_graph=0)
+for i in ids:
+    g.set_occupancy(i, np.full(32768, 255, np.uint8))
+g.train(1, ids, [1 << 20] * 32, stats=False)
+assert fake.fake_threads(b"k_live") > 0
+""")
