@@ -169,7 +169,8 @@ __device__ inline float div_fixed(float a, float b, float r) {
 // Unit-cube coordinates of an object-frame point: p = (x + a) / 2a clamped to
 // [0, 1] (clamped before dividing, which gives the same values: division is
 // monotonic, and a NaN clamps to 0 either way).  inv: 1 / 2a, or zeros for a
-// box outside div_fixed's range.
+// box outside div_fixed's range, where 2a may be infinite: then a clamped
+// x + a may be too, and the quotient, a NaN, is clamped to 0.
 __device__ inline void unit_pos(const float x[3], const float* half, const float* inv, float p[3]) {
   float n[3], w[3];
 #pragma unroll
@@ -182,7 +183,7 @@ __device__ inline void unit_pos(const float x[3], const float* half, const float
     for (int k = 0; k < 3; ++k) p[k] = div_fixed(n[k], w[k], inv[k]);
   } else {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) p[k] = n[k] / w[k];
+    for (int k = 0; k < 3; ++k) p[k] = __builtin_amdgcn_fmed3f(n[k] / w[k], 0.0f, 1.0f);
   }
 }
 
