@@ -1136,9 +1136,9 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
     uint32_t idx[4];
     float2 av[4];
     int rank[4];
-    uint32_t sw = 0u;
+    float s = 0.0f;  // the smaller x weight
+    const uint32_t m = T - 1u;
     if (has) {
-      const uint32_t m = T - 1u;
       const uint32_t ya = cl.c[1] * 2654435761u, za = cl.c[2] * 805459861u;
       const uint32_t yb = ya + 2654435761u, zb = za + 805459861u;
       const bool up = cl.f[0] > 0.5f;  // the corner at c_x + 1 takes the larger weight
@@ -1151,14 +1151,15 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
       const float w[4] = {gy * gz, cl.f[1] * gz, gy * cl.f[2], cl.f[1] * cl.f[2]};
 #pragma unroll
       for (int q = 0; q < 4; ++q) av[q] = make_float2(w[q] * g.x, w[q] * g.y);
-      const uint32_t diff = (cl.c[0] ^ (cl.c[0] + 1u)) & m;  // 2^kind - 1
-      sw = pair_sword(up ? 1.0f - cl.f[0] : cl.f[0], (uint32_t)__popc(diff));
+      s = up ? 1.0f - cl.f[0] : cl.f[0];
 #pragma unroll
       for (int q = 0; q < 4; ++q) rank[q] = atomicAdd(&lcnt[idx[q] >> RB], 1);
     }
     const int n = place();
     int4* stage = (int4*)dyn;  // slot within the pair's records, then the record
     if (has) {
+      const uint32_t diff = (cl.c[0] ^ (cl.c[0] + 1u)) & m;  // 2^kind - 1
+      const uint32_t sw = pair_sword(s, (uint32_t)__popc(diff));
       int2 b[4];  // all four first: one LDS round trip
 #pragma unroll
       for (int q = 0; q < 4; ++q) b[q] = rg[idx[q] >> RB];
@@ -1170,9 +1171,8 @@ __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8)))
         stage[b[q].x + rank[q]] =
             make_int4(fits ? (int)(idx[q] >> RB) * cap + slot : -1, __float_as_int(r.ax),
                       __float_as_int(r.ay), __float_as_int(r.s));
-        if (!fits) {  // bin full: direct atomics (correct, only slower)
-          const float s = pair_s(r);
-          const uint32_t o = idx[q] ^ ((cl.c[0] ^ (cl.c[0] + 1u)) & (T - 1u));
+        if (!fits) {  // bin full: direct atomics of the unrounded values (only slower)
+          const uint32_t o = idx[q] ^ diff;
           unsafeAtomicAdd(gl + 2 * (int64_t)idx[q], (1.0f - s) * av[q].x);
           unsafeAtomicAdd(gl + 2 * (int64_t)idx[q] + 1, (1.0f - s) * av[q].y);
           unsafeAtomicAdd(gl + 2 * (int64_t)o, s * av[q].x);
