@@ -1330,16 +1330,14 @@ __device__ inline void rec_add(unsigned long long* acc, const uint32_t* emax, fl
   fx_add(acc, emax, rec_entry(x, y), rec_value(x), rec_value(y));
 }
 
-// Pair records: the exponent of A bounds the (1 - s) A entry's (half of it
-// at least), and s A < 2^(eA - 126) 2^(es - 126).
+// Pair records: of the products that pair_add takes (a sum of the factors'
+// exponents may be one above, and would cost the sums a bit).
 __device__ inline void pair_max(uint32_t* emax, const PairRec& r) {
   uint32_t e, o;
   pair_entries(r, e, o);
-  const uint32_t ea = max(exp_field(r.ax), exp_field(r.ay));
-  const int es = (int)((__float_as_uint(r.s) >> 23) & 0x7fu);
-  const int eo = ea == 0xffu ? 0xff : max((int)ea + es - 126, 0);
-  atomicMax(&emax[e], ea);
-  atomicMax(&emax[o], (uint32_t)eo);
+  const float s = pair_s(r), t = 1.0f - s, ax = pair_a(r.ax), ay = pair_a(r.ay);
+  atomicMax(&emax[e], max(exp_field(t * ax), exp_field(t * ay)));
+  atomicMax(&emax[o], max(exp_field(s * ax), exp_field(s * ay)));
 }
 
 __device__ inline void pair_add(unsigned long long* acc, const uint32_t* emax, const PairRec& r) {

@@ -86,3 +86,25 @@ def test_overflow_takes_the_whole_split():
     assert err.size > 500
     assert err.max() < 2.01 * (2.0 ** -19 + 2.0 ** -21)
     assert off <= 128
+
+
+def test_sums_hold_38_bits_below_the_largest_term():
+    """A region's fixed-point sums keep each term to half a unit of 2^-38 of the
+    power of two at or below the entry's largest term.  Three equal rays with
+    adjoints 1, -1 and 2^-34 leave 2^-34 of a single ray's value: the large
+    terms round alike and cancel, so the small one's rounding is all that is
+    off (the records and products scale exactly with a power of two)."""
+    print("fixed-point bits", flush=True)
+    g, i, rays, adj = _setup(60, 11)
+    small, large, _, alone = _pairs(rays)
+    one = _grad(g, i, rays, adj)
+    k = 2.0 ** -34
+    three = _grad(g, i, rays.repeat(3, 0),
+                  np.stack([adj, -adj, adj * np.float32(k)], 1).reshape(-1, 3))
+    e = np.concatenate([small[alone], large[alone]])
+    e = e[(one[e] != 0).all(1)]
+    unit = 2.0 ** (np.floor(np.log2(np.abs(one[e]).max(1))) - 38)
+    err = np.abs(three[e] - k * one[e]).max(1) / unit
+    print(f"  {e.size} entries, off by up to {err.max():.3f} units, {int((err > 0.5).sum())} by more than half")
+    assert e.size > 1000
+    assert err.max() <= 0.5
