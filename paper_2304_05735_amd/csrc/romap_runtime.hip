@@ -1675,10 +1675,8 @@ romap_status romap_render(romap_ctx* c, int32_t id, const romap_camera* cam, flo
     d_depth = depth ? c->d_image + 3 * npix : nullptr;
     d_opac = opacity ? c->d_image + 4 * npix : nullptr;
   }
-  if (!c->d_hits) {
-    HIPALLOC(c, hipMalloc((void**)&c->d_hits, sizeof(int)));
-    HIPALLOC(c, hipHostMalloc((void**)&c->h_hits, sizeof(int), hipHostMallocDefault));
-  }
+  if (!c->d_hits) HIPALLOC(c, hipMalloc((void**)&c->d_hits, sizeof(int)));
+  if (!c->h_hits) HIPALLOC(c, hipHostMalloc((void**)&c->h_hits, sizeof(int), hipHostMallocDefault));
   const int NS = c->cfg.samples_per_ray, K1 = K1_of(c->cfg);
   // pixels per pass (their ray records: 64 MiB) and hit rays per launch (their
   // encodings: 512 MiB at 16 levels)

@@ -145,3 +145,12 @@ for i in ids:
 g.train(1, ids, [1 << 20] * 32, stats=False)
 assert fake.fake_threads(b"k_live") > 0
 """)
+
+
+def test_render_after_a_failed_host_allocation(fake):
+    fake("""
+g, (i,), cam = context()
+fake.fake_fail_host_malloc(1)
+assert code(lambda: g.render(i, cam)) == pk.ROMAP_E_OUT_OF_MEMORY
+assert code(lambda: g.render(i, cam)) == 0 and code(lambda: g.render(i, cam)) == 0
+""")
