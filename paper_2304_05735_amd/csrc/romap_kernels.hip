@@ -949,7 +949,7 @@ __device__ inline float pair_s(const PairRec& r) {
 __device__ inline float pair_a(float x) { return __uint_as_float(__float_as_uint(x) & ~0x1Fu); }
 
 // Stores of data that no kernel reads back while it could still be in the
-// L2 (gradient records, read by the next kernel after the whole scatter;
+// L2 (corner records, read by the next kernel after the whole scatter;
 // parameters and moments after their Adam update): written past the L2's
 // allocation (measured: the accumulation that follows runs 6 % faster).
 __device__ inline void nt_store2(float2* p, float2 v) {
@@ -1023,7 +1023,7 @@ __device__ inline bool chain_step(float2 v[8], uint32_t& open) {
 }
 
 // Exclusive scan of cnt[0..n) into at[0..n).x by a whole block of WG threads
-// (n <= 8 * WG); returns the total to every thread.  at[j].y of the thread's
+// (n / WG entries each); returns the total to every thread.  at[j].y of the thread's
 // own entry (n <= WG) is set to y.
 template <int WG>
 __device__ inline int block_exclusive_scan(const int* cnt, int2* at, int n, int y, int* s_wsum) {
@@ -1070,7 +1070,8 @@ __device__ inline int block_exclusive_scan(const int* cnt, int2* at, int n, int 
 // next block of the same XCD completes the lines.
 // Staging: 32 KB, so that four blocks fit a CU: all pair records, and
 // RM_STAGE_CORNERS corner records (a block's further ones, on levels where
-// hardly any merge, are stored straight to their slots).
+// hardly any merge, are stored straight to their slots).  Four blocks also
+// leave a thread 64 registers: 4 of them spill (16 B of scratch a lane).
 template <int NS, int RB>
 __global__ __launch_bounds__(RM_SCAT_WG) __attribute__((amdgpu_waves_per_eu(8))) void k_bin_scatter(
     StepArgs a) {
@@ -1807,7 +1808,8 @@ __device__ inline void load_e_b(const uint32_t* e, int64_t S, int64_t s, int L, 
 // (one before: 97 KB; 4096 rays x 64 samples 138 -> 112 us).
 // FWD: colour, depth and T_end only (RM_MODE_FORWARD): without the backward
 // half's registers and operands several waves share a SIMD and hide the
-// layers' latency (the same rays: FP32 44 -> 32 us).
+// layers' latency (the same rays: FP32 44 -> 32 us).  At 128 samples its two
+// words of a ray's live mask, indexed by block, lie in 32 B of scratch a lane.
 template <int PREC, int NS, int K1, int NH, bool FWD>
 #ifndef RM_FIELD_BF16_WAVES
 #define RM_FIELD_BF16_WAVES 2

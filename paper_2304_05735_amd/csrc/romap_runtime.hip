@@ -41,11 +41,15 @@ constexpr int64_t kMaxSamplesPerObject = int64_t(1) << 27;
 constexpr int64_t kMaxRaysPerCall = int64_t(1) << 30;
 
 // Threads of a gather workgroup (512 samples) where the autotuner has no say.
-// Up to about 16 rounds of resident workgroups one 64-sample chunk per wave
-// (4096 rays x 64 samples at 16 levels: 162 us the call against 163 with 256
-// threads and 167 with 128); beyond, four, so that a wave's first loads and
-// the chunks without live samples (missing rays, skipped space) cost less
-// (22663 camera rays x 128 samples: 885, 808 and 785 us).
+// Up to about 16 rounds of resident workgroups 512, one 64-sample chunk per
+// wave (16 levels of 2^19 entries, the kernel with 128, 256 and 512 threads:
+// 4096 rays x 64 samples 87, 83 and 81 us, 1999 x 128 69, 65 and 65); beyond,
+// 128, four chunks per wave, so that a wave's first loads and the chunks
+// without live samples cost less (22663 rays x 128 samples 527, 538 and 576 us;
+// a 173 x 131 view x 128 samples with 30 % of the cells occupied, the call, 312
+// against 368 us with 512).  Long launches of 64-sample rays with nothing
+// skipped hardly care (65536 rays 986, 979 and 973 us; a 640 x 480 view 908
+// against 914 with 512).
 int gather_block(const StepArgs& a) { return a.n_bblocks > 16384 ? 128 : 512; }
 
 // Rays per workgroup of the field kernel in the calls on one object's caller-
@@ -778,14 +782,13 @@ hipError_t accumulate_phases(romap_ctx* c) {
 // How a call's objects are spread over plans.
 enum PlanKind { kPlanAll = 0, kPlanHalves = 1, kPlanPerObject = 2 };
 
-void split_list(romap_ctx* c, const std::vector<std::pair<int, int>>& list,
-                std::vector<std::pair<int, int>> half[2]);
-
 // The plans of a call, staged: c->staged.  They follow from the objects (their
 // levels never change), the ray counts, the launch shape and the bin cap, so a
 // call of the same as the last finds them in place: no work lists are built,
 // nothing is copied and the host does not wait for the stream (a training loop
 // around the differentiable surface: each call waited for the one before).
+// Only the last call's are kept: objects or ray counts that change from call to
+// call, and renders in between, are staged again each time.
 romap_status stage_cached(romap_ctx* c, const std::vector<std::pair<int, int>>& list, PlanKind kind,
                           int rpi, int blk) {
   std::vector<int64_t> sig = {kind, rpi, blk, c->debug_bin_cap};
