@@ -8,8 +8,9 @@ with respect to the parameter vector (grid level-major, then W1..W4).  Only
 the parameter tensor and the rays are kept between the two passes.
 
 The context must order its work on torch's current stream (create it with
-``stream=torch.cuda.current_stream()``), so that the library's kernels and
-torch's own operations on the same tensors are ordered.
+``stream=torch.cuda.current_stream()``, torch's default stream or another), so
+that the library's kernels and torch's own operations on the same tensors are
+ordered.
 """
 from __future__ import annotations
 
